@@ -123,7 +123,7 @@ gdn_status launch_intra(const gdn_shape& s, const Plan& p, const int32_t* cu, co
 // second half's transition) also fits runs split, which halves the chain.
 // When the 32-wide grid does not fit, tail replay of bf16 inputs takes the
 // wide column scan (two tiles per wave, two workgroups per CU: throughput) and
-// everything else the whole-head scan.
+// everything else the 64-column scan with output waves or the whole-head scan.
 gdn_status cols_fit(const gdn_shape& s, bool* fits, uint32_t* col_groups, int* cus_out = nullptr) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -159,7 +159,7 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
       hipLaunchKernelGGL((k_scan_cols_split<TIn, DK>), dim3(static_cast<uint32_t>(split_groups(s))),
                          dim3(cols_split_threads()), 0, stream,
                          static_cast<int32_t>(split_first_groups(s)), cu, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k),
-                         static_cast<const TIn*>(q), Kw, Tw, Sw, state_out, m2, a2);
+                         Kw, Tw, Sw, state_out, m2, a2);
       if ((st = check_launch("split scan launch")) != GDN_OK) return st;
       if (marks && (st = mark(*marks, 2)) != GDN_OK) return st;
       if (combined) *combined = true;
@@ -192,7 +192,7 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
                        static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in,
                        static_cast<TIn*>(o), state_out);
   } else if constexpr (kColsOut) {
-    hipLaunchKernelGGL((k_scan_cols_out_ord<TIn, DK>), dim3(col_groups), dim3(cols_threads(true, true)), 0, stream,
+    hipLaunchKernelGGL((k_scan_cols_out_ord<TIn, DK, 2>), dim3(col_groups), dim3(cols_threads(true, true)), 0, stream,
                        cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(v),
                        static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in,
                        static_cast<TIn*>(o), state_out);
@@ -205,8 +205,7 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
     if (groups64 <= 3 * static_cast<int64_t>(cus)) {
       hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(groups64)),
                          dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
-                         s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw,
-                         Tw, Sw, state_out);
+                         s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
       return check_launch("scan launch");
     }
     // Otherwise a whole head per workgroup (128 columns, four compute waves)
@@ -225,8 +224,7 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
     const int32_t n_wide = s.num_seqs - peel;
     hipLaunchKernelGGL((k_scan_cols_wide<TIn, DK, kCols>), dim3(static_cast<uint32_t>(n_wide * per_seq)),
                        dim3(cols_wide_threads(kCols)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v,
-                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
-                       state_out);
+                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
     if (peel > 0) {
       if ((st = check_launch("scan launch")) != GDN_OK) return st;
       SeqOrder po;
@@ -235,43 +233,58 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
       hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(peel) * s.num_v_heads *
                                                            (s.d_v / kSplitCols2)),
                          dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, po, s.num_k_heads, s.num_v_heads, s.d_v,
-                         static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw,
-                         Sw, state_out);
+                         static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
     }
-  } else {
-    // a whole head per workgroup, one per CU.  With outputs, when the grid's
-    // last round would be partly empty and its sequences (the shortest, in
-    // longest-first order) fit in two rounds of the 32-column scan with
-    // output waves, they run in that after the whole-head grid (12 and 36
-    // sequences of 32 heads, 16 chunks: 216 -> 205 and 557 -> 545 us).
-    int32_t peel = 0;
-    if constexpr (FWD) {
+  } else if constexpr (kNarrow) {
+    // bf16 with outputs.  A batch whose 64-column grid fits on the chip at
+    // once, and every batch at d_v = 64 (where a head is one such workgroup),
+    // takes it: at 4 sequences of 32 heads and 64 chunks the scan takes 197 us
+    // so, 311 us with a head per workgroup; at d_v = 64 and 12 or 24 sequences
+    // of 16 chunks 100 and 173 us against 119 and 214.  Beyond one round at
+    // d_v = 128 the head per workgroup is ahead (8 sequences: 89 against 102
+    // us, 36: 440 against 488), except for the sequences of a partly empty last
+    // round (the shortest, in longest-first order) that fit on the chip in the
+    // 64-column form: those run in it after the rest (12 sequences: 95 + 59 us
+    // against 162 for all of them in it).
+    const int64_t per_head = s.d_v / kOutCols;
+    const int64_t groups = static_cast<int64_t>(s.num_seqs) * s.num_v_heads * per_head;
+    const auto launch_out = [&](const SeqOrder& order, int64_t seqs) {
+      hipLaunchKernelGGL((k_scan_cols_out_ord<TIn, DK, kOutTiles>),
+                         dim3(static_cast<uint32_t>(seqs * s.num_v_heads * per_head)),
+                         dim3(cols_threads(true, false, kOutTiles)), 0, stream, cu, order, s.num_k_heads,
+                         s.num_v_heads, s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k),
+                         static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in, static_cast<TIn*>(o), state_out);
+    };
+    if (DV == kOutCols || groups <= cus) {
+      launch_out(p.order, s.num_seqs);
+      return check_launch("scan launch");
+    }
+    if constexpr (DV > kOutCols) {
+      int32_t peel = 0;
       const int64_t rem = static_cast<int64_t>(s.num_seqs) * s.num_v_heads % cus;
       if (rem > 0 && s.num_seqs <= kMaxOrderedSeqs) {
         peel = static_cast<int32_t>((rem + s.num_v_heads - 1) / s.num_v_heads);
-        if (peel >= s.num_seqs ||
-            static_cast<int64_t>(peel) * s.num_v_heads * (s.d_v / kColsPerGroup) > 2 * static_cast<int64_t>(cus))
-          peel = 0;
+        if (peel >= s.num_seqs || static_cast<int64_t>(peel) * s.num_v_heads * per_head > cus) peel = 0;
       }
-    }
-    const int32_t n_head = s.num_seqs - peel;
-    hipLaunchKernelGGL((k_scan_head<TIn, DK, DV, FWD>), dim3(static_cast<uint32_t>(n_head) * s.num_v_heads),
-                       dim3(head_threads(DV)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
-                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
-                       Pw, state_in, static_cast<TIn*>(o), state_out);
-    if constexpr (FWD) {
+      const int32_t n_head = s.num_seqs - peel;
+      hipLaunchKernelGGL((k_scan_head<TIn, DK, DV, FWD>), dim3(static_cast<uint32_t>(n_head) * s.num_v_heads),
+                         dim3(head_threads(DV)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
+                         static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
+                         Pw, state_in, static_cast<TIn*>(o), state_out);
       if (peel > 0) {
         if ((st = check_launch("scan launch")) != GDN_OK) return st;
         SeqOrder po;
         po.n = peel;
         for (int32_t i = 0; i < peel; ++i) po.seq[i] = p.order.n > 0 ? p.order.seq[n_head + i] : n_head + i;
-        hipLaunchKernelGGL((k_scan_cols_out_ord<TIn, DK>),
-                           dim3(static_cast<uint32_t>(peel) * s.num_v_heads * (s.d_v / kColsPerGroup)),
-                           dim3(cols_threads(true, sizeof(TIn) == 4)), 0, stream, cu, po, s.num_k_heads,
-                           s.num_v_heads, s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k),
-                           static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in, static_cast<TIn*>(o), state_out);
+        launch_out(po, peel);
       }
     }
+  } else {
+    // fp32 tail replay: a whole head per workgroup, one per CU
+    hipLaunchKernelGGL((k_scan_head<TIn, DK, DV, FWD>), dim3(static_cast<uint32_t>(s.num_seqs) * s.num_v_heads),
+                       dim3(head_threads(DV)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
+                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
+                       Pw, state_in, static_cast<TIn*>(o), state_out);
   }
   return check_launch("scan launch");
 }
@@ -469,7 +482,7 @@ gdn_status run_fused(const FusedArgs& a) {
       hipLaunchKernelGGL((k_scan_cols_split<TIn, DK>), dim3(static_cast<uint32_t>(split_groups(s))),
                          dim3(cols_split_threads()), 0, a.stream,
                          static_cast<int32_t>(split_first_groups(s)), a.cu_t, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(a.v_t),
-                         static_cast<const TIn*>(a.k_t), static_cast<const TIn*>(nullptr),
+                         static_cast<const TIn*>(a.k_t),
                          reinterpret_cast<const u32x4*>(a.ws_t + pt.off_K),
                          reinterpret_cast<const u32x4*>(a.ws_t + pt.off_T),
                          reinterpret_cast<const float*>(a.ws_t + pt.off_S), a.state_mid,

@@ -158,6 +158,25 @@ __device__ __forceinline__ int kslot(int l) { return (l & 48) | ((l + 4 * (l >> 
 // The lane whose 16 bytes sit at position p (the inverse of kslot).
 __device__ __forceinline__ int kslot_inv(int p) { return (p & 48) | ((p + 16 - 4 * (p >> 4)) & 15); }
 
+// ---------------------------------------------------------------- key rows in LDS
+// bf16 key (and query) rows lie in LDS as they lie in memory, RB = 2 d_k bytes
+// a row, with the 16-byte pieces of row r at positions piece ^ row_swz(r).
+// Whole rows are what the DMA fetches best: 1 KiB as 4 rows of 256 bytes keeps
+// the CU's vector memory path busy for 34 clocks, as the 16 rows x 64 bytes of
+// an operand fragment for 78 (measured at a row stride of 64 KiB).  With the
+// swizzle a 16-byte operand read, which takes lanes {0-3, 12-15, 20-23, 24-27},
+// {4-7, 8-11, 16-19, 28-31} (and the same of the upper half) at a time, is free
+// of bank conflicts, and a transposing 8-byte read, 32 consecutive lanes at a
+// time, meets each bank twice, the least there is (its lanes all want the same
+// half of their 16 bytes).
+// Linear over XOR: row_swz(a ^ b) = row_swz(a) ^ row_swz(b).
+template <int RB>
+__device__ __forceinline__ constexpr int row_swz(int r) {
+  static_assert(RB == 128 || RB == 256, "rows of 64 or 128 bf16");
+  const int hi = (r >> 3) & 1;
+  return RB == 256 ? ((2 * r) & 14) ^ (9 * hi) : (r & 6) ^ (5 * hi);
+}
+
 // ---------------------------------------------------------------- state row order
 // The scan holds the state M (d_k x d_v) in MFMA accumulator tiles of 16 rows.
 // Lane (g, c) holds rows 4g..4g+3 of tile td, which are state rows

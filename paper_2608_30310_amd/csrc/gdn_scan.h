@@ -17,16 +17,18 @@
 // model of exactly these roundings; dropping any other pass (hi(M0) alone in
 // K M0, or the lo part of R, Delta or P) takes it past 1e-3 somewhere.
 //
-// Every A operand except P (K, K^T, Q, T) comes from a workspace record that
-// k_intra wrote in fragment order, copied global -> LDS by DMA (global_load_lds,
-// 16 bytes per lane) into one of two LDS buffers while the waves compute on the
-// other; each wave issues an equal share of the next chunk's DMA at the start
-// of a chunk and waits for it at the end.  A wave then fetches each operand
-// with one conflict-free 16-byte LDS read; V uses the transposing LDS read; P
-// (outputs only) comes straight from global memory into registers.  Two waves
-// per SIMD let one wave's VALU work (hi/lo splits) run while the other's MFMAs
-// run.  Inside a chunk the waves issue each group of LDS reads one region
-// ahead of its use.
+// A chunk's operands come global -> LDS by DMA (global_load_lds, 16 bytes per
+// lane) into one of two LDS buffers while the waves compute on the other: the
+// key, query and value rows from the inputs (bf16; for fp32 inputs keys and
+// queries from a record of hi and lo fragments), T, P and the scalars from the
+// records k_intra wrote.  A wave fetches each operand with 16-byte or
+// transposing LDS reads whose addresses are a lane constant plus an immediate
+// (the chunk loop takes the two buffers in turn, see each_chunk).  Inside a
+// chunk the waves issue each group of LDS reads one region ahead of its use.
+//
+// What bounds it: a chunk is a chain of dependent products, and a wave issues
+// its ~290 vector and 76 MFMA instructions of 16 columns in order, one every
+// ~5.5 clocks (3.2k clocks a chunk, of which the matrix pipe is busy 1.2k).
 #pragma once
 
 #include "gdn_device.h"
@@ -58,12 +60,19 @@ __device__ __forceinline__ void dma16_at(const void* base, uint32_t off, lds_byt
 }
 
 
-// Byte offset of byte `byte_in_row` of row `row` in a row tile whose rows hold
-// ROW_BYTES / 16 pieces of 16 bytes, piece p of row R stored at p ^ (R % pieces).
+// Byte offset of byte `byte_in_row` of row `row` in a value row tile whose rows
+// hold ROW_BYTES / 16 pieces of 16 bytes, piece p of row R stored at p ^
+// v_swz(R): the transposing reads (32 lanes, eight rows of two pieces, at a
+// time) then touch every bank once.
+template <int ROW_BYTES>
+__device__ __forceinline__ constexpr int v_swz(int row) {
+  if (ROW_BYTES == 256) return row_swz<256>(row);
+  if (ROW_BYTES == 64) return 2 * ((row >> 2) & 1);
+  return row % (ROW_BYTES / 16);
+}
 template <int ROW_BYTES>
 __device__ __forceinline__ int swz(int row, int byte_in_row) {
-  constexpr int pieces = ROW_BYTES / 16;
-  return row * ROW_BYTES + 16 * ((byte_in_row / 16) ^ (row % pieces)) + byte_in_row % 16;
+  return row * ROW_BYTES + 16 * ((byte_in_row / 16) ^ v_swz<ROW_BYTES>(row)) + byte_in_row % 16;
 }
 
 // DMA of rows [0, 64) of a token-major tensor (row 0 at `row0`, 1 KiB block
@@ -75,7 +84,7 @@ __device__ __forceinline__ void dma_rows(const T* row0, int64_t row_stride, int 
   constexpr int pieces = ROW_BYTES / 16;
   constexpr int rows_per_block = 1024 / ROW_BYTES;
   const int r = blk * rows_per_block + lane / pieces;
-  const int p = (lane % pieces) ^ (r % pieces);
+  const int p = (lane % pieces) ^ v_swz<ROW_BYTES>(r);
   const uint32_t stride_b = static_cast<uint32_t>(row_stride) * static_cast<uint32_t>(sizeof(T));
   dma16_at(row0, static_cast<uint32_t>(min(r, rows - 1)) * stride_b + 16u * p, dst + blk * 1024);
 }
@@ -143,25 +152,11 @@ struct ChunkSrc {
   int clen;                    // valid rows
 };
 
-// DMA job j of a chunk (0 <= j < L::kJobs) into LDS buffer `base`.
+// DMA job j of a chunk of fp32 inputs (0 <= j < L::kJobs) into LDS buffer `base`.
 template <typename L, typename TIn>
 __device__ __forceinline__ void dma_job(const ChunkSrc& c, int64_t vrow, lds_byte* base, int j, int lane) {
   if (j < L::kKJobs) {
-    if constexpr (L::kSplit) {
-      dma16_at(c.krec + 1024 * j, 16u * lane, base + L::kOffK + 1024 * j);
-    } else {
-      // fragment j: keys for j < 4 d_k/32, then queries; the lane at position
-      // `lane` (kslot order) takes 16 bytes of row 16 ti + r at column 32 kk +
-      // 8 g; pad rows repeat the last row (their beta is 0, so they add nothing)
-      constexpr int NK = L::kDK / 32, NKA = ka_frags(L::kDK);
-      const bool isq = j >= NKA;
-      const int f = isq ? j - NKA : j;
-      const int l = kslot_inv(lane);
-      const int row = min(16 * (f / NK) + (l & 15), c.clen - 1);
-      const uint32_t krow_b = static_cast<uint32_t>(c.krow) * 2u;
-      dma16_at(static_cast<const uint16_t*>(isq ? c.q0 : c.k0) + 32 * (f % NK),
-               static_cast<uint32_t>(row) * krow_b + 16u * (l >> 4), base + L::kOffK + 1024 * j);
-    }
+    dma16_at(c.krec + 1024 * j, 16u * lane, base + L::kOffK + 1024 * j);
   } else if (j < L::kKJobs + L::kTJobs) {
     const int t = j - L::kKJobs;
     dma16_at(c.trec + 1024 * t, 16u * lane, base + L::kOffT + 1024 * t);
@@ -179,10 +174,36 @@ __device__ __forceinline__ void dma_job(const ChunkSrc& c, int64_t vrow, lds_byt
   }
 }
 
+// A chunk's key rows in LDS (bf16 inputs; rows 64.. are the queries), as MFMA
+// operands.
+template <int DK>
+struct KeyTile {
+  static constexpr int kRB = 2 * DK;
+  const unsigned char* rows;
+  int lane;
+  // A operand of K M0 (and B operand of (Q M0)^T): lane (g, r) gets columns 32
+  // kk + 8 g .. +7 of row 16 ti + r.
+  __device__ __forceinline__ bf16x8 frag(int ti, int kk) const {
+    const int lg = lane / 16, lr = lane % 16;
+    return *reinterpret_cast<const bf16x8*>(rows + (16 * ti + lr) * kRB + 16 * ((4 * kk + lg) ^ row_swz<kRB>(lr)));
+  }
+  // A operand of K^T Delta by transposing reads: lane (g, c) needs K[32 kk +
+  // kperm(g, j)][column c of state row tile td] (see strow).  In a transposing
+  // read each lane of a 16-lane group addresses four consecutive columns of one
+  // row and receives one column of four rows; lane (g, c) addresses row 32 kk +
+  // 4 g + c / 4 (then 16 rows further, for j >= 4), columns strow(td, c % 4, 0..3).
+  __device__ __forceinline__ bf16x8 frag_t(int td, int kk) const {
+    const int lg = lane / 16, lr = lane % 16;
+    const int rr = 4 * lg + lr / 4;
+    const unsigned char* p = rows + (32 * kk + rr) * kRB + 16 * ((4 * (td / 2) + lr % 4) ^ row_swz<kRB>(rr)) +
+                             8 * (td % 2);
+    return __builtin_bit_cast(bf16x8, join_halves(lds_read_tr16(p), lds_read_tr16(p + 16 * kRB)));
+  }
+};
+
 // One 64-token chunk for one wave: 16 state columns, M (and its split mb) in
 // registers.  `base` is the chunk's LDS buffer, `vc0` the wave's first column
-// within the buffer's V tile, `pg` the chunk's P record in global memory
-// (outputs only, used when the layout does not stage P in LDS).  The chunk runs as a chain of regions: each region issues the
+// within the buffer's V tile.  The chunk runs as a chain of regions: each region issues the
 // LDS reads of a later region, runs MFMAs on operands that are ready, and does
 // VALU work (scaling, hi/lo splits) for the next region that is independent of
 // its own MFMAs.  hook(k) runs at the start of region k (the whole-head kernel
@@ -193,7 +214,7 @@ __device__ __forceinline__ void dma_job(const ChunkSrc& c, int64_t vrow, lds_byt
 // the split of M1 (the next chunk's B operand of K M0, layout [k step][hi |
 // lo][lane]) to `xm` at the end.
 template <typename L, int DK, bool FWD, bool EXPORT, typename Hook>
-__device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, const u32x4* pg, int lane,
+__device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, int lane,
                                            f32x4 (&M)[DK / 16], Frag (&mb)[DK / 32], f32x4 (&pout)[4],
                                            Hook&& hook, unsigned char* xd = nullptr,
                                            unsigned char* xm = nullptr) {
@@ -211,9 +232,15 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   // fragment f of the K record (`nf` fragments per bf16 part; the lo part
   // exists for fp32 inputs only), lanes in kslot order
   const int klane = kslot(lane);
-  auto ldf = [&](Frag& x, const u32x4* rec, int f, int nf) __attribute__((always_inline)) {
-    x.hi = __builtin_bit_cast(bf16x8, rec[f * kWave + klane]);
-    if constexpr (SPLIT) x.lo = __builtin_bit_cast(bf16x8, rec[(nf + f) * kWave + klane]);
+  const KeyTile<DK> kt{base + L::kOffK, lane};   // bf16 inputs: the rows themselves
+  auto ldf = [&](Frag& x, int ti, int kk, bool isq) __attribute__((always_inline)) {
+    if constexpr (SPLIT) {
+      const int f = (isq ? NKA : 0) + ti * NK + kk;
+      x.hi = __builtin_bit_cast(bf16x8, kf[f * kWave + klane]);
+      x.lo = __builtin_bit_cast(bf16x8, kf[(NKF + f) * kWave + klane]);
+    } else {
+      x.hi = kt.frag(ti + (isq ? 4 : 0), kk);
+    }
   };
   // fp32-derived records: P always hi and lo, T hi (and lo for fp32 inputs)
   auto ld_split = [&](Frag& x, const u32x4* rec, int f) __attribute__((always_inline)) {
@@ -239,27 +266,26 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
-        ldf(a[u][kk], kf, (2 * tp + u) * NK + kk, NKF);
-        if constexpr (FWD) ldf(aq[u][kk], kf, NKA + (2 * tp + u) * NK + kk, NKF);
+        ldf(a[u][kk], 2 * tp + u, kk, false);
+        if constexpr (FWD) ldf(aq[u][kk], 2 * tp + u, kk, true);
       }
   };
   // K^T operands of every row tile td of M for token k step kk, by
-  // transposing reads of the K fragments: lane (g, c) needs K[32 kk +
-  // kperm(g, j)][16 td + c].  In a transposing read each lane of a 16-lane
-  // group addresses four consecutive columns of one row and receives one
-  // column of four rows; lane (g, c) addresses row 32 kk + 4 g + c / 4
-  // (then 16 rows further, for j >= 4), columns 16 td + 4 (c % 4)..+3: in K
-  // fragment (row tile 2 kk (+1), k step td / 2) that is lane 16 (c % 4) +
-  // 4 g + c / 4 (at its kslot position), bytes 8 (td % 2)..+7.
+  // transposing reads of the keys (see KeyTile): lane (g, c) addresses row 32 kk
+  // + 4 g + c / 4, columns strow(td, c % 4, 0..3); in K record fragment (row tile
+  // 2 kk (+1), k step td / 2) that is lane 16 (c % 4) + 4 g + c / 4 (at its kslot
+  // position), bytes 8 (td % 2)..+7.
   const int kt_off = 16 * kslot(16 * (lr % 4) + 4 * lg + lr / 4);
   auto ld_kt = [&](Frag (&a)[NT], int kk) __attribute__((always_inline)) {
 #pragma unroll
     for (int td = 0; td < NT; ++td) {
-      const unsigned char* f0 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk) * NK + td / 2) * kWave);
-      const unsigned char* f1 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk + 1) * NK + td / 2) * kWave);
-      const int o = kt_off + 8 * (td % 2);
-      a[td].hi = __builtin_bit_cast(bf16x8, join_halves(lds_read_tr16(f0 + o), lds_read_tr16(f1 + o)));
-      if constexpr (SPLIT) {
+      if constexpr (!SPLIT) {
+        a[td].hi = kt.frag_t(td, kk);
+      } else {
+        const unsigned char* f0 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk) * NK + td / 2) * kWave);
+        const unsigned char* f1 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk + 1) * NK + td / 2) * kWave);
+        const int o = kt_off + 8 * (td % 2);
+        a[td].hi = __builtin_bit_cast(bf16x8, join_halves(lds_read_tr16(f0 + o), lds_read_tr16(f1 + o)));
         constexpr int lo = NKF * kWave * 16;
         a[td].lo = __builtin_bit_cast(bf16x8, join_halves(lds_read_tr16(f0 + lo + o), lds_read_tr16(f1 + lo + o)));
       }
@@ -272,7 +298,7 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   // so the two overlap.
   Frag ka0[2][NK], qa0[2][NK], ka1[2][NK], qa1[2][NK];
   Frag tfr[kTFrags];
-  Frag kt0[NT], kt1[NT];
+  Frag kta[NT], ktb[NT];
   f32x4 km[4], qm[4], bv[4], R[4], D[4];
   u32x2 vraw[4];
   float vf[4][4];
@@ -344,21 +370,14 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   hook(3);
   // ---- region 3: Delta = T R, k step 0 for all row tiles | R rows 32..63
   //      and their split; K^T (k step 0) and P (outputs) arrive
-  ld_kt(kt0, 0);
+  ld_kt(kta, 0);
   Frag pfr[FWD ? kTFrags : 1];
   if constexpr (FWD) {
-    // P (fp32-derived: hi and lo parts), staged in LDS or straight from global
-    if constexpr (L::kPInLds) {
-      const u32x4* pl = reinterpret_cast<const u32x4*>(base + L::kOffP);
+    // P (fp32-derived: hi and lo parts)
+    static_assert(L::kPInLds, "a wave that forms its own outputs reads P from LDS");
+    const u32x4* pl = reinterpret_cast<const u32x4*>(base + L::kOffP);
 #pragma unroll
-      for (int f = 0; f < kTFrags; ++f) ld_split(pfr[f], pl, f);
-    } else {
-#pragma unroll
-      for (int f = 0; f < kTFrags; ++f) {
-        pfr[f].hi = __builtin_bit_cast(bf16x8, pg[f * kWave + lane]);
-        pfr[f].lo = __builtin_bit_cast(bf16x8, pg[(kTFrags + f) * kWave + lane]);
-      }
-    }
+    for (int f = 0; f < kTFrags; ++f) ld_split(pfr[f], pl, f);
   }
 #pragma unroll
   for (int ti = 0; ti < 4; ++ti) D[ti] = mma_tr(tfr[tri_frag(ti, 0)], rb0, zero4());
@@ -371,7 +390,7 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   // ---- region 4: Delta, k step 1 for row tiles 2, 3 | split of the
   //      weighted Delta rows 0..31 (and of Delta for the outputs); K^T
   //      arrives
-  ld_kt(kt1, 1);
+  ld_kt(ktb, 1);
   if constexpr (EXPORT) {
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) reinterpret_cast<f32x4*>(xd)[ti * kWave + lane] = D[ti];   // final
@@ -403,7 +422,7 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   for (int td = 0; td < NT; ++td) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) M[td][r] *= eg;
-    M[td] = mma_a<SPLIT>(kt0[td], db0, M[td]);
+    M[td] = mma_a<SPLIT>(kta[td], db0, M[td]);
   }
   make_dw(2);
   make_dw(3);
@@ -434,8 +453,8 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, c
   // ---- region 6: M1, k step 1 (tokens 32..63) | split of M1 for the next chunk
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    M[2 * kk] = mma_a<SPLIT>(kt1[2 * kk], db1, M[2 * kk]);
-    M[2 * kk + 1] = mma_a<SPLIT>(kt1[2 * kk + 1], db1, M[2 * kk + 1]);
+    M[2 * kk] = mma_a<SPLIT>(ktb[2 * kk], db1, M[2 * kk]);
+    M[2 * kk + 1] = mma_a<SPLIT>(ktb[2 * kk + 1], db1, M[2 * kk + 1]);
     mb[kk] = chain_frag(M[2 * kk], M[2 * kk + 1]);
   }
   if constexpr (EXPORT) {
@@ -468,23 +487,10 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
   constexpr int NT = DK / 16, NK = DK / 32;
   constexpr int VRB = L::kVRowBytes;
   const int lg = lane / 16, lr = lane % 16;
-  const u32x4* kf = reinterpret_cast<const u32x4*>(base + L::kOffK);
   const u32x4* tf = reinterpret_cast<const u32x4*>(base + L::kOffT);
   const float* sc = reinterpret_cast<const float*>(base + L::kOffS);
   const unsigned char* vtile = base + L::kOffV;
-  const int klane = kslot(lane);
-  // K fragment of row tile ti, k step kk (lanes in kslot order)
-  auto ldk = [&](int ti, int kk) __attribute__((always_inline)) {
-    return __builtin_bit_cast(bf16x8, kf[(ti * NK + kk) * kWave + klane]);
-  };
-  // K^T operand of row tile td of M for token k step kk (as in chunk_step)
-  const int kt_off = 16 * kslot(16 * (lr % 4) + 4 * lg + lr / 4);
-  auto ldkt = [&](int td, int kk) __attribute__((always_inline)) {
-    const unsigned char* f0 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk) * NK + td / 2) * kWave);
-    const unsigned char* f1 = reinterpret_cast<const unsigned char*>(kf + ((2 * kk + 1) * NK + td / 2) * kWave);
-    const int o = kt_off + 8 * (td % 2);
-    return __builtin_bit_cast(bf16x8, join_halves(lds_read_tr16(f0 + o), lds_read_tr16(f1 + o)));
-  };
+  const KeyTile<DK> kt{base + L::kOffK, lane};
 
   // ---- V (transposing reads: lane (g, c) gets V[16 ti + 4 g + r][c]) and the
   //      first k step's K
@@ -497,7 +503,7 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
       vraw[c][ti] = lds_read_tr16(vtile + swz<VRB>(16 * ti + 4 * lg + lr / 4, 2 * (vc0 + 16 * c + 4 * (lr % 4))));
   bf16x8 ka[2][4];
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti) ka[0][ti] = ldk(ti, 0);
+  for (int ti = 0; ti < 4; ++ti) ka[0][ti] = kt.frag(ti, 0);
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- K M0, one k step at a time; the next step's K (after the last, T) arrives
@@ -508,7 +514,7 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
     hook(1 + kk);
     if (kk + 1 < NK) {
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) ka[(kk + 1) & 1][ti] = ldk(ti, kk + 1);
+      for (int ti = 0; ti < 4; ++ti) ka[(kk + 1) & 1][ti] = kt.frag(ti, kk + 1);
     } else {
 #pragma unroll
       for (int f = 0; f < kTFrags; ++f) tfr[f] = __builtin_bit_cast(bf16x8, tf[f * kWave + lane]);
@@ -546,7 +552,7 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
   // ---- Delta = hi(T) R, k step 0 | R rows 32..63; K^T for tokens 0..31 arrives
   hook(NK + 2);
 #pragma unroll
-  for (int td = 0; td < NT; ++td) kt0[td] = ldkt(td, 0);
+  for (int td = 0; td < NT; ++td) kt0[td] = kt.frag_t(td, 0);
   f32x4 D[NC][4];
 #pragma unroll
   for (int ti = 0; ti < 4; ++ti)
@@ -559,7 +565,7 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
   //      split; K^T for tokens 32..63 arrives
   hook(NK + 3);
 #pragma unroll
-  for (int td = 0; td < NT; ++td) kt1[td] = ldkt(td, 1);
+  for (int td = 0; td < NT; ++td) kt1[td] = kt.frag_t(td, 1);
 #pragma unroll
   for (int ti = 2; ti < 4; ++ti)
 #pragma unroll
@@ -607,6 +613,19 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
     }
 }
 
+// f(j, b) for chunks j = 0 .. n - 1, b (a compile-time constant) the LDS buffer
+// of chunk j.  With two buffers the loop takes two chunks a turn, so every LDS
+// address of a chunk is a lane address that never changes plus a constant.
+template <int BUFFERS, typename F>
+__device__ __forceinline__ void each_chunk(int n, F&& f) {
+  for (int j = 0; j < n; j += BUFFERS) {
+    f(j, std::integral_constant<int, 0>{});
+    if constexpr (BUFFERS == 2) {
+      if (j + 1 < n) f(j + 1, std::integral_constant<int, 1>{});
+    }
+  }
+}
+
 // Shared set-up of a scan workgroup for sequence n, value head h, state
 // columns [col0, col0 + VC).
 struct ScanUnit {
@@ -650,6 +669,175 @@ __device__ __forceinline__ ChunkSrc chunk_src(const ScanUnit& u, int ci, int hk,
   return c;
 }
 
+// The DMA of a bf16 scan's chunks, one after the other, as issued by wave w of
+// NW: its share is the same jobs every chunk (key, query and value row blocks
+// w, w + NW, .., then T blocks and scalars), so a chunk costs it a few scalar
+// additions and four vector instructions per row block.  With the addresses
+// formed anew for every job, the issuing waves of the wide scan spent ~250
+// scalar instructions and two dozen branches a chunk on them.
+template <typename L, int NW, bool FWD>
+struct ScanDma {
+  static_assert(!L::kSplit, "key rows come from the inputs");
+  static_assert(L::kOffP == L::kOffT + 1024 * L::kTJobs && L::kOffS == L::kOffP + 1024 * L::kPJobs, "T, P, scalars");
+  static constexpr int kRB = 2 * L::kDK, kKPieces = kRB / 16, kKRows = 1024 / kRB;   // key rows
+  static constexpr int kKBlocks = kChunk * kRB / 1024;
+  // eight waves: four fetch the keys, four the queries
+  static constexpr int kKW = NW == 8 ? 4 : NW;
+  static_assert(kKBlocks % kKW == 0 && (NW <= 4 || (NW == 8 && FWD)), "equal shares of the key rows");
+  static constexpr int kKPer = kKBlocks / kKW;
+  static constexpr int kKQ = kKPer * (FWD && NW <= 4 ? 2 : 1);
+  static constexpr int kPieces = L::kVRowBytes / 16, kRowsPerBlock = 1024 / L::kVRowBytes;
+  static constexpr int kVPer = (L::kVJobs + NW - 1) / NW;
+  static constexpr int kTP = L::kTJobs + L::kPJobs;
+  static constexpr int kTSPer = (kTP + 2 + NW - 1) / NW;   // T blocks, P blocks if any, then the scalars' two
+  static constexpr int kPerWave = kKQ + kVPer + kTSPer;
+
+  int w, lane;
+  int left;                               // rows from the chunk's first to the sequence's end
+  uint32_t krow_b, vrow_b, t_b, p_b, s_b; // bytes between rows, and between chunks' records
+  const unsigned char *k, *q, *v, *t, *p, *s;   // the chunk's first rows and records
+  uint32_t krow, kpiece, vrow, vpiece;    // this lane's row and piece of the wave's first row blocks
+
+  __device__ __forceinline__ void start(const ScanUnit& u, int ci, int wave, int lane_, int hk, int hv, int dv,
+                                        int col0, const uint16_t* vin, const uint16_t* kin, const uint16_t* qin,
+                                        const u32x4* Kw, const u32x4* Tw, const float* Sw, const u32x4* Pw) {
+    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, dv, col0, vin, kin, qin, Kw, Tw, Sw, Pw);
+    w = wave;
+    lane = lane_;
+    left = u.len - ci * kChunk;
+    krow_b = static_cast<uint32_t>(hk) * kRB;
+    vrow_b = static_cast<uint32_t>(hv) * static_cast<uint32_t>(dv) * 2u;
+    t_b = static_cast<uint32_t>(hv) * L::kTBytes;
+    p_b = static_cast<uint32_t>(hv) * static_cast<uint32_t>(kPRecordBytes);
+    s_b = static_cast<uint32_t>(hv) * L::kSBytes;
+    k = static_cast<const unsigned char*>(NW == 8 && w >= 4 ? c.q0 : c.k0);
+    q = static_cast<const unsigned char*>(c.q0);
+    v = static_cast<const unsigned char*>(c.v0);
+    t = c.trec;
+    p = c.prec;
+    s = c.srow;
+    krow = (w % kKW) * kKRows + lane / kKPieces;
+    kpiece = 16u * ((lane % kKPieces) ^ row_swz<kRB>(krow));
+    vrow = w * kRowsPerBlock + lane / kPieces;
+    vpiece = 16u * ((lane % kPieces) ^ v_swz<L::kVRowBytes>(vrow));
+  }
+  // Lane offset of row `row` (rows past the chunk's end repeat the last valid
+  // row: their beta is 0, so they add nothing).  Strides are below 2^24: at
+  // most 65535 heads of 128 bf16.
+  __device__ __forceinline__ uint32_t row_off(uint32_t row, uint32_t stride_b, uint32_t piece) const {
+    return __umul24(min(row, static_cast<uint32_t>(min(kChunk, left) - 1)), stride_b) + piece;
+  }
+  // Job J of the wave's share into LDS buffer `base`; `values` false: no value rows.
+  template <int J>
+  __device__ __forceinline__ void job(lds_byte* base, bool values = true) const {
+    if constexpr (J < kKQ) {
+      constexpr int i = J % kKPer, row = i * kKW * kKRows;
+      constexpr bool isq = J >= kKPer;    // queries after the keys
+      const int blk = w % kKW + kKW * i + (isq || (NW == 8 && w >= 4) ? kKBlocks : 0);
+      dma16_at(isq ? q : k, row_off(krow + row, krow_b, kpiece ^ (16u * row_swz<kRB>(row))),
+               base + L::kOffK + 1024 * blk);
+    } else if constexpr (J < kKQ + kVPer) {
+      constexpr int i = J - kKQ, row = i * NW * kRowsPerBlock;
+      const int blk = w + NW * i;
+      if (values && (L::kVJobs % NW == 0 || blk < L::kVJobs))
+        dma16_at(v, row_off(vrow + row, vrow_b, vpiece ^ (16u * v_swz<L::kVRowBytes>(row))),
+                 base + L::kOffV + 1024 * blk);
+    } else {
+      // block of T, then of P, then of the scalars (1 KiB and 256 bytes)
+      const int x = w * kTSPer + (J - kKQ - kVPer);
+      const unsigned char* src = x < L::kTJobs ? t + 1024 * x : x < kTP ? p + 1024 * (x - L::kTJobs) : s + 1024 * (x - kTP);
+      if (x <= kTP || (x == kTP + 1 && lane < 16)) dma16_at(src, 16u * lane, base + L::kOffT + 1024 * x);
+    }
+  }
+  template <int J0, int J1>
+  __device__ __forceinline__ void jobs(lds_byte* base, bool values = true) const {
+    if constexpr (J0 < J1) {
+      job<J0>(base, values);
+      jobs<J0 + 1, J1>(base, values);
+    }
+  }
+  __device__ __forceinline__ void next() {
+    k += static_cast<uint64_t>(krow_b) * kChunk;
+    q += static_cast<uint64_t>(krow_b) * kChunk;
+    v += static_cast<uint64_t>(vrow_b) * kChunk;
+    t += t_b;
+    p += p_b;
+    s += s_b;
+    left -= kChunk;
+  }
+  // A whole chunk's share, and on to the next chunk.
+  __device__ __forceinline__ void chunk(lds_byte* base, bool values = true) {
+    jobs<0, kPerWave>(base, values);
+    next();
+  }
+  // The p-th of N parts of it (p a constant in each instance).
+  template <int N, int P = 0>
+  __device__ __forceinline__ void phase(int p, lds_byte* base) {
+    if constexpr (P < N) {
+      if (p == P) {
+        jobs<P * kPerWave / N, (P + 1) * kPerWave / N>(base);
+        if (P == N - 1) next();
+      } else {
+        phase<N, P + 1>(p, base);
+      }
+    }
+  }
+};
+
+// The same for fp32 inputs, whose K record is contiguous: wave w takes jobs w,
+// w + NW, ..
+template <typename L, typename TIn, int NW>
+struct RecordDma {
+  static constexpr int kPerWave = (L::kJobs + NW - 1) / NW;
+  ChunkSrc c;
+  int w, lane, left;
+  int64_t vrow, k_b, t_b, p_b, s_b;   // elements between value rows; bytes between chunks' records
+  __device__ __forceinline__ void start(const ScanUnit& u, int ci, int wave, int lane_, int hk, int hv, int dv,
+                                        int col0, const TIn* vin, const TIn* kin, const TIn* qin, const u32x4* Kw,
+                                        const u32x4* Tw, const float* Sw, const u32x4* Pw) {
+    c = chunk_src<L>(u, ci, hk, hv, dv, col0, vin, kin, qin, Kw, Tw, Sw, Pw);
+    w = wave;
+    lane = lane_;
+    left = u.len - ci * kChunk;
+    vrow = static_cast<int64_t>(hv) * dv;
+    k_b = static_cast<int64_t>(hk) * L::kKBytes;
+    t_b = static_cast<int64_t>(hv) * L::kTBytes;
+    p_b = static_cast<int64_t>(hv) * static_cast<int64_t>(kPRecordBytes);
+    s_b = static_cast<int64_t>(hv) * L::kSBytes;
+  }
+  __device__ __forceinline__ void jobs(lds_byte* base, int j0, int j1) const {
+#pragma unroll
+    for (int jj = j0; jj < j1; ++jj) {
+      const int j = w + NW * jj;
+      if (j < L::kJobs) dma_job<L, TIn>(c, vrow, base, j, lane);
+    }
+  }
+  __device__ __forceinline__ void next() {
+    c.krec += k_b;
+    c.trec += t_b;
+    c.prec += p_b;
+    c.srow += s_b;
+    c.v0 = static_cast<const TIn*>(c.v0) + vrow * kChunk;
+    left -= kChunk;
+    c.clen = min(kChunk, left);
+  }
+  __device__ __forceinline__ void chunk(lds_byte* base, bool = true) {
+    jobs(base, 0, kPerWave);
+    next();
+  }
+  template <int N>
+  __device__ __forceinline__ void phase(int p, lds_byte* base) {
+    if (p < N) jobs(base, p * kPerWave / N, (p + 1) * kPerWave / N);
+    if (p == N - 1) next();
+  }
+};
+template <typename L, typename TIn, int NW, bool FWD>
+struct ChunkDmaOf { using type = ScanDma<L, NW, FWD>; };
+template <typename L, int NW, bool FWD>
+struct ChunkDmaOf<L, float, NW, FWD> { using type = RecordDma<L, float, NW>; };
+template <typename L, typename TIn, int NW, bool FWD>
+using ChunkDma = typename ChunkDmaOf<L, TIn, NW, FWD>::type;
+
 // Per-wave state load/store and the deferred output store.
 template <int DK>
 __device__ __forceinline__ void load_state(const float* __restrict__ state_in, int64_t sbase, int dv, int lg,
@@ -688,16 +876,26 @@ __device__ __forceinline__ void store_chunk_out(TIn* o, const ScanUnit& u, int c
 // state to two output waves (one per 16 columns), so the outputs' products
 // stay off the sequential chain, and a fifth wave issues the DMA.
 constexpr int kColsPerGroup = 32;
-// With outputs, bf16 inputs get a dedicated DMA wave; for fp32 inputs the
-// recurrence wave needs ~250 VGPRs, more than two waves sharing a SIMD may
-// hold, so the two output waves issue the DMA instead (4 waves).
-constexpr bool cols_dma_wave(bool fwd, bool split) { return fwd && !split; }
+// With outputs: roles of the workgroup's waves (waves go to the four SIMDs in
+// turn).
+constexpr int kOutTiles = 4, kOutCols = 16 * kOutTiles;   // of a throughput workgroup with outputs
+enum ColsRole { kRoleChain, kRoleOut, kRoleDma, kRoleIdle };
+constexpr int cols_dma_waves(bool split, int tiles) { return split || tiles == kOutTiles ? 0 : 1; }
 constexpr int cols_threads(bool fwd, bool split, int tiles = 2) {
-  return (fwd ? (split ? 4 : 1 + 2 * tiles) : 3) * kWave;
+  return (fwd ? 2 * tiles + cols_dma_waves(split, tiles) : 3) * kWave;
+}
+// DMA wave first, then the recurrence waves, then the output waves.
+__device__ __forceinline__ int cols_role(bool split, int tiles, int wave) {
+  const int x = wave - cols_dma_waves(split, tiles);
+  return x < 0 ? kRoleDma : x < tiles ? kRoleChain : kRoleOut;
+}
+__device__ __forceinline__ int cols_tile(bool split, int tiles, int wave) {
+  const int x = wave - cols_dma_waves(split, tiles);
+  return x < 0 ? 0 : x % tiles;
 }
 
-template <typename TIn, int DK, bool FWD, int COLS = kColsPerGroup>
-using ColsLds = ScanLds<TIn, DK, COLS, FWD, true>;
+template <typename TIn, int DK, int COLS = kColsPerGroup>
+using ColsLds = ScanLds<TIn, DK, COLS, false, false>;
 
 // Tail replay of bf16 inputs whose grid does not fit on the chip at once (a
 // throughput batch) runs the wide column scan: COLS = 128 columns (a whole
@@ -709,6 +907,7 @@ using ColsLds = ScanLds<TIn, DK, COLS, FWD, true>;
 // 1.25x the columns per CU per unit time of the 64-column workgroup of four
 // one-tile waves and a DMA wave it replaces.
 constexpr int kWideTiles = 2;   // 16-column tiles per compute wave
+constexpr int kDmaPhases = 4;   // parts of a chunk over which its compute waves issue the next one's DMA
 constexpr int cols_wide_threads(int cols) { return cols / (16 * kWideTiles) * kWave; }
 
 // Tail replay in two halves: the recurrence over a chunk is affine in the
@@ -740,25 +939,20 @@ __device__ __forceinline__ int split_point(int nch) { return (27 * nch + 25) / 5
 // further waves only take part in the barriers; without, the compute waves
 // issue the next chunk's DMA themselves, a share at each phase of the chunk
 // (multi-tile steps only).
-template <typename TIn, int DK, bool FWD, int COLS = kColsPerGroup, int PART = kWhole, int NC = 1,
-          bool DMA_WAVE = true>
+template <typename TIn, int DK, int COLS = kColsPerGroup, int PART = kWhole, int NC = 1, bool DMA_WAVE = true>
 __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int nblocks,
                                                const int32_t* __restrict__ cu, int32_t hk, int32_t hv,
                                                int32_t dv, const TIn* __restrict__ v,
-                                               const TIn* __restrict__ kin, const TIn* __restrict__ qin,
-                                               const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
-                                               const float* __restrict__ Sw, const u32x4* __restrict__ Pw,
-                                               const float* __restrict__ state_in, TIn* __restrict__ o,
+                                               const TIn* __restrict__ kin, const u32x4* __restrict__ Kw,
+                                               const u32x4* __restrict__ Tw, const float* __restrict__ Sw,
                                                float* __restrict__ state_out, SplitOut split = {},
                                                const SeqOrder* order = nullptr) {
-  using L = ColsLds<TIn, DK, FWD, COLS>;
+  using L = ColsLds<TIn, DK, COLS>;
   constexpr bool SPLIT = PART != kWhole;
-  static_assert(!(SPLIT && FWD), "the split form is tail replay only");
   constexpr int NT = DK / 16;
   constexpr int CW = COLS / (16 * NC);   // compute waves
   static_assert(CW * 16 * NC == COLS, "whole column tiles per wave");
   static_assert(DMA_WAVE || NC > 1, "the compute waves issue the DMA in multi-tile steps");
-  constexpr int kVJob0 = L::kKJobs + L::kTJobs + L::kPJobs;   // first V job
   const int tid = threadIdx.x;
   // wave index made provably uniform: DMA destinations (M0) stay scalar
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -789,27 +983,13 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
   }
   const int col0 = COLS * g;
   const int colw = col0 + 16 * NC * wave;   // the wave's first column; tile c: colw + 16 c + lr
-  const int64_t vrow = static_cast<int64_t>(hv) * dv;
-  auto dma_chunk = [&](int ci, int b) __attribute__((always_inline)) {
-    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, dv, ident ? 0 : col0, v, kin, qin, Kw, Tw, Sw, Pw);
-#pragma unroll
-    for (int j = 0; j < L::kJobs; ++j) {
-      // the transition's value rows are the zeros written below
-      if (SPLIT && ident && j >= kVJob0 && j < kVJob0 + L::kVJobs) continue;
-      dma_job<L, TIn>(c, vrow, lds_l + b * L::kBytes, j, lane);
-    }
-  };
-  // without a DMA wave: this compute wave's jobs wave + CW jj, jj in [j0, j1)
-  constexpr int PER_WAVE = (L::kJobs + CW - 1) / CW;
-  auto dma_share = [&](int ci, int b, int j0, int j1) __attribute__((always_inline)) {
-    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, dv, ident ? 0 : col0, v, kin, qin, Kw, Tw, Sw, Pw);
-#pragma unroll
-    for (int jj = j0; jj < j1; ++jj) {
-      const int j = wave + CW * jj;
-      if (j >= L::kJobs || (SPLIT && ident && j >= kVJob0 && j < kVJob0 + L::kVJobs)) continue;
-      dma_job<L, TIn>(c, vrow, lds_l + b * L::kBytes, j, lane);
-    }
-  };
+  // the chunks' DMA, in order: all of it on the DMA wave, or an equal share on
+  // each compute wave (the transition's value rows are the zeros written below)
+  constexpr int NI = DMA_WAVE ? 1 : CW;
+  ChunkDma<L, TIn, NI, false> dma;
+  if (DMA_WAVE ? dma_wave : true)
+    dma.start(u, cb, DMA_WAVE ? 0 : wave, lane, hk, hv, dv, ident ? 0 : col0, v, kin, nullptr, Kw, Tw, Sw,
+              nullptr);
 
   const int64_t sbase = (static_cast<int64_t>(u.n) * hv + u.h) * DK * ld + colw + lr;   // tile c: + 16 c
   if (SPLIT && ident) {
@@ -825,20 +1005,20 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
   // the compute waves' loop alone.
   if (data_wave) {
     if (dma_wave && nch > 0) {
-      dma_chunk(cb, 0);
+      dma.chunk(lds_l, !ident);
       wait_dma();
     }
     __syncthreads();
     for (int j = 0; j < nch; ++j) {
       const int b = L::kBuffers == 2 ? (j & 1) : 0;
       if (dma_wave && L::kBuffers == 2 && j + 1 < nch) {
-        dma_chunk(cb + j + 1, b ^ 1);   // lands while the compute waves work on buffer b
+        dma.chunk(lds_l + (b ^ 1) * L::kBytes, !ident);   // lands while the compute waves work on buffer b
         wait_dma();
       }
       if (L::kBuffers == 1) {
         __syncthreads();   // the compute waves are done with the only buffer
         if (dma_wave && j + 1 < nch) {
-          dma_chunk(cb + j + 1, 0);
+          dma.chunk(lds_l, !ident);
           wait_dma();
         }
       }
@@ -849,7 +1029,6 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
 
   f32x4 M[NC][NT];
   Frag mb[NC][DK / 32];
-  f32x4 pout[4];
   if (SPLIT && ident) {
     // M0 = identity columns
 #pragma unroll
@@ -864,45 +1043,38 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
   } else {
 #pragma unroll
     for (int c = 0; c < NC; ++c)
-      load_state<DK>(SPLIT ? nullptr : state_in, sbase + 16 * c, ld, lg, M[c], mb[c]);
+      load_state<DK>(nullptr, 0, ld, lg, M[c], mb[c]);
   }
   if (!DMA_WAVE && nch > 0) {
-    dma_share(cb, 0, 0, PER_WAVE);
+    dma.chunk(lds_l, !ident);
     wait_dma();
   }
   __syncthreads();
-  for (int j = 0; j < nch; ++j) {
-    const int ci = cb + j;
-    const int b = L::kBuffers == 2 ? (j & 1) : 0;
-    if constexpr (FWD) {
-      if (j > 0) store_chunk_out(o, u, ci - 1, hv, dv, colw, lane, pout);
-    }
-    const u32x4* pg = FWD ? Pw + (static_cast<int64_t>(u.slot0 + ci) * hv + u.h) * (2 * kTFrags * kWave) : nullptr;
+  each_chunk<L::kBuffers>(nch, [&](int j, auto bc) __attribute__((always_inline)) {
+    constexpr int b = decltype(bc)::value;
     const unsigned char* buf = (const unsigned char*)(lds_l + b * L::kBytes);
     if constexpr (NC > 1) {
       // without a DMA wave: the next chunk's share, spread over the phases
       const bool prefetch = !DMA_WAVE && L::kBuffers == 2 && j + 1 < nch;
-      constexpr int NPH = tiles_phases(DK);
       chunk_step_tiles<L, DK, NC>(buf, 16 * NC * wave, lane, M, mb, [&](int p) __attribute__((always_inline)) {
-        const int j0 = p * PER_WAVE / NPH, j1 = (p + 1) * PER_WAVE / NPH;
-        if (prefetch && j1 > j0) dma_share(ci + 1, b ^ 1, j0, j1);
+        if constexpr (!DMA_WAVE) {
+          if (prefetch) dma.template phase<kDmaPhases>(p, lds_l + (b ^ 1) * L::kBytes);
+        }
       });
       if (!DMA_WAVE) wait_dma();   // this wave's share of the next chunk has landed
     } else {
-      chunk_step<L, DK, FWD, false>(buf, 16 * wave, pg, lane, M[0], mb[0], pout, [](int) {});
+      f32x4 none[4];
+      chunk_step<L, DK, false, false>(buf, 16 * wave, lane, M[0], mb[0], none, [](int) {});
     }
     if (L::kBuffers == 1) {
       __syncthreads();   // done with the only buffer
       if (!DMA_WAVE && j + 1 < nch) {
-        dma_share(ci + 1, 0, 0, PER_WAVE);
+        dma.chunk(lds_l, !ident);
         wait_dma();
       }
     }
     __syncthreads();     // next chunk's operands are in LDS (every wave's share)
-  }
-  if constexpr (FWD) {
-    if (nch > 0) store_chunk_out(o, u, ce - 1, hv, dv, colw, lane, pout);
-  }
+  });
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     if (SPLIT && ident) {
@@ -937,23 +1109,14 @@ struct ColsOutLayout {
 };
 
 // One column-split workgroup with outputs (block `block` of `nblocks`), LDS in
-// `lds_l`.  Two waves carry the recurrence of columns 16 c.. (chunk_step
+// `lds_l`: TILES waves carry the recurrence of 16 columns each (chunk_step
 // without outputs, exporting Delta before its region 5 and the split of M1 at
-// its end) and two write the outputs of the same columns:
+// its end) and TILES waves write the outputs of the same columns:
 //   before the mid-chunk barrier: (Q M0)^T from the split M0 of the chunk;
 //   after it: O^T = diag-scaled (Q M0)^T + Delta^T P^T, stored at the start
 //   of the next chunk.
-// With a DMA wave (bf16 inputs): wave 0 issues the next chunk's DMA (two
-// thirds before the mid-chunk barrier, the rest after it), waves 1 + c carry
-// the recurrence, waves 3 + c write the outputs; with waves assigned to SIMDs
-// in turn, the DMA wave shares a SIMD with an output wave and each recurrence
-// wave has one to itself.  Without (fp32 inputs): waves c carry the
-// recurrence, waves 2 + c write the outputs and each issues half of the DMA.
 // The products are those of chunk_step with outputs, in the same order, so the
-// results are the same bit for bit.  TILES = 1 (bf16 inputs): a 16-column
-// workgroup of a DMA wave, one recurrence wave and one output wave, for grids
-// that fit on the chip at one workgroup per CU even so (each recurrence wave
-// then has a CU's LDS bandwidth to itself).
+// results are the same bit for bit.
 template <typename TIn, int DK, int TILES = 2>
 __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, int nblocks,
                                                    const int32_t* __restrict__ cu, int32_t hk, int32_t hv,
@@ -970,20 +1133,16 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
   constexpr int NT = DK / 16, NK = DK / 32;
   constexpr int NKA = ka_frags(DK);
   constexpr int NKF = L::kKFrags;
-  constexpr bool DMA_WAVE = cols_dma_wave(true, SPLIT);
-  static_assert(TILES == 2 || (TILES == 1 && DMA_WAVE), "one tile per workgroup needs the DMA wave");
-  constexpr int kEarlyJobs = 2 * L::kJobs / 3;   // DMA jobs issued before the mid-chunk barrier
-  static_assert(DMA_WAVE || (L::kKJobs % 2 == 0 && L::kTJobs % 2 == 0 && L::kPJobs == 0 &&
-                             L::kVJobs % 2 == 0), "DMA halves need records of whole multiples of 2 KiB");
-  constexpr int kHalf = (L::kKJobs + L::kTJobs + L::kVJobs) / 2;   // jobs per output wave, scalars aside
+  constexpr int DW = cols_dma_waves(SPLIT, TILES);
+  constexpr bool TWO = CL::kBuffers == 2;
+  static_assert(TILES == 2 || !SPLIT, "fp32 inputs: two tiles per workgroup");
+  static_assert(TWO || DW == 0, "a DMA wave fills the other buffer");
   const int tid = threadIdx.x;
   // wave index made provably uniform: DMA destinations (M0) stay scalar
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int first_chain = DMA_WAVE ? 1 : 0;
-  const bool dma_wave = DMA_WAVE && wave == 0;
-  const bool chain_wave = wave >= first_chain && wave < first_chain + TILES;
-  const bool out_wave = wave >= first_chain + TILES;
-  const int tile = (wave - first_chain) % TILES, h = tile;
+  const int role = cols_role(SPLIT, TILES, wave);
+  const int tile = cols_tile(SPLIT, TILES, wave);
+  const bool issues = role == (DW > 0 ? kRoleDma : kRoleOut);
   const int lane = tid % kWave, lg = lane / 16, lr = lane % 16;
   constexpr int COLS = 16 * TILES;
   const int ngroups = dv / COLS;
@@ -993,53 +1152,27 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
   const int col0 = COLS * (unit % ngroups);
   const ScanUnit u = scan_unit(cu, unit / (ngroups * hv), (unit / ngroups) % hv, hv, hk, order);
   const int colw = col0 + 16 * tile;
-  const int64_t vrow = static_cast<int64_t>(hv) * dv;
   unsigned char* xd = (unsigned char*)(lds_l + CL::kOffX + tile * CL::kTileBytes);
   unsigned char* xm = xd + CL::kDBytes;
 
-  // DMA jobs [j0, j1) of chunk ci into buffer b (the job index is a
-  // compile-time constant in each instance, so every job is straight code)
-  auto dma_jobs = [&](int ci, int b, auto j0c, auto j1c) __attribute__((always_inline)) {
-    constexpr int j0 = decltype(j0c)::value, j1 = decltype(j1c)::value;
-    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, dv, col0, v, kin, qin, Kw, Tw, Sw, Pw);
-#pragma unroll
-    for (int j = j0; j < j1; ++j) dma_job<L, TIn>(c, vrow, lds_l + b * L::kBytes, j, lane);
-  };
-  using J0 = std::integral_constant<int, 0>;
-  using JE = std::integral_constant<int, kEarlyJobs>;
-  using JN = std::integral_constant<int, L::kJobs>;
-  // without a DMA wave: jobs 2 q + h of the K record, the T record and the V
-  // rows for q in [q0, q1) (every record is a multiple of two jobs, so which
-  // record a job reads is known at compile time); the scalars with the
-  // second half
-  auto dma_half = [&](int ci, int b, int q0, int q1) __attribute__((always_inline)) {
-    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, dv, col0, v, kin, qin, Kw, Tw, Sw, Pw);
-    lds_byte* dst = lds_l + b * L::kBytes;
-#pragma unroll
-    for (int q = q0; q < q1; ++q) {
-      if (q < L::kKJobs / 2) {
-        const int j = 2 * q + h;
-        dma16_at(c.krec + 1024 * j, 16u * lane, dst + L::kOffK + 1024 * j);
-      } else if (q < (L::kKJobs + L::kTJobs) / 2) {
-        const int j = 2 * (q - L::kKJobs / 2) + h;
-        dma16_at(c.trec + 1024 * j, 16u * lane, dst + L::kOffT + 1024 * j);
-      } else {
-        // V rows; pad rows repeat the last row (their beta is 0, so they add nothing)
-        dma_rows<L::kVRowBytes>(static_cast<const TIn*>(c.v0), vrow, c.clen, dst + L::kOffV,
-                                2 * (q - (L::kKJobs + L::kTJobs) / 2) + h, lane);
-      }
-    }
-    if (q1 == kHalf) {
-      if (h == 0) dma16_at(c.srow, 16u * lane, dst + L::kOffS);                       // bytes 0..1023
-      else if (lane < 16) dma16_at(c.srow + 1024, 16u * lane, dst + L::kOffS + 1024); // 1024..1279
-    }
-  };
+  ChunkDma<L, TIn, (DW > 0 ? DW : TILES), true> dma;
+  if (issues) dma.start(u, 0, tile, lane, hk, hv, dv, col0, v, kin, qin, Kw, Tw, Sw, Pw);
 
-  f32x4 M[NT];
-  Frag mb[NK];
-  f32x4 pout[4];
-  const int64_t sbase = (static_cast<int64_t>(u.n) * hv + u.h) * DK * dv + colw + lr;
-  if (chain_wave) {
+  // each role runs a loop of its own with the same barriers
+  if (issues && u.nch > 0) dma.chunk(lds_l);
+  auto chunk_end = [&](int ci) __attribute__((always_inline)) {
+    if (!TWO) {
+      lds_barrier();   // every wave is done with the only buffer
+      if (issues && ci + 1 < u.nch) dma.chunk(lds_l);
+    }
+    if (issues) wait_dma();
+    lds_barrier();     // next chunk's operands are in LDS; this buffer is free
+  };
+  if (role == kRoleChain) {
+    f32x4 M[NT];
+    Frag mb[NK];
+    f32x4 none[4];
+    const int64_t sbase = (static_cast<int64_t>(u.n) * hv + u.h) * DK * dv + colw + lr;
     load_state<DK>(state_in, sbase, dv, lg, M, mb);
     u32x4* x = reinterpret_cast<u32x4*>(xm);
 #pragma unroll
@@ -1047,35 +1180,49 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
       x[(2 * kk) * kWave + lane] = __builtin_bit_cast(u32x4, mb[kk].hi);
       x[(2 * kk + 1) * kWave + lane] = __builtin_bit_cast(u32x4, mb[kk].lo);
     }
-  } else if (u.nch > 0) {
-    if (dma_wave) {
-      dma_jobs(0, 0, J0{}, JN{});
-      wait_dma();
-    } else if (!DMA_WAVE) {
-      dma_half(0, 0, 0, kHalf);
-      wait_dma();
-    }
-  }
-  __syncthreads();
-  for (int ci = 0; ci < u.nch; ++ci) {
-    const int b = CL::kBuffers == 2 ? (ci & 1) : 0;
-    const unsigned char* base = (const unsigned char*)(lds_l + b * L::kBytes);
-    const bool prefetch = CL::kBuffers == 2 && ci + 1 < u.nch;
-    if (chain_wave) {
-      chunk_step<L, DK, false, true>(base, 16 * tile, nullptr, lane, M, mb, pout,
+    lds_barrier();
+    each_chunk<CL::kBuffers>(u.nch, [&](int ci, auto bc) __attribute__((always_inline)) {
+      const unsigned char* base = (const unsigned char*)(lds_l + decltype(bc)::value * L::kBytes);
+      chunk_step<L, DK, false, true>(base, 16 * tile, lane, M, mb, none,
                                      [](int k) __attribute__((always_inline)) {
                                        if (k == 5) lds_barrier();   // Delta is out
                                      },
                                      xd, xm);
-    } else if (dma_wave) {
-      if (prefetch) dma_jobs(ci + 1, b ^ 1, J0{}, JE{});
-      lds_barrier();
-      if (prefetch) dma_jobs(ci + 1, b ^ 1, JE{}, JN{});
-    } else {
+      chunk_end(ci);
+    });
+    if (state_out) {
+#pragma unroll
+      for (int td = 0; td < NT; ++td)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          state_out[sbase + static_cast<int64_t>(strow(td, lg, r)) * dv] = M[td][r];
+    }
+  } else if (role == kRoleOut) {
+    f32x4 pout[4];
+    if (issues) wait_dma();
+    lds_barrier();
+    each_chunk<CL::kBuffers>(u.nch, [&](int ci, auto bc) __attribute__((always_inline)) {
+      constexpr int b = decltype(bc)::value;
+      const unsigned char* base = (const unsigned char*)(lds_l + b * L::kBytes);
+      // P (split, six nonzero fragments) from global memory
+      const u32x4* pg = Pw + (static_cast<int64_t>(u.slot0 + ci) * hv + u.h) * (2 * kTFrags * kWave);
+      Frag pfr[kTFrags];
+      auto load_p = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < kTFrags; ++f) {
+          pfr[f].hi = __builtin_bit_cast(bf16x8, pg[f * kWave + lane]);
+          pfr[f].lo = __builtin_bit_cast(bf16x8, pg[(kTFrags + f) * kWave + lane]);
+        }
+      };
+      if (TILES == kOutTiles) {
+        load_p();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (DW == 0 && TWO && ci + 1 < u.nch) dma.chunk(lds_l + (b ^ 1) * L::kBytes);
       if (ci > 0) store_chunk_out(o, u, ci - 1, hv, dv, colw, lane, pout);
-      if (!DMA_WAVE && prefetch) dma_half(ci + 1, b ^ 1, 0, kHalf / 2);
       // (Q M0)^T: A = split M0 from the recurrence wave, B = Q fragments
       const u32x4* kf = reinterpret_cast<const u32x4*>(base + L::kOffK);
+      const KeyTile<DK> qt{base + L::kOffK, lane};
       const u32x4* x = reinterpret_cast<const u32x4*>(xm);
       Frag m0[NK];
 #pragma unroll
@@ -1090,22 +1237,19 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
         Frag qa[NK];
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
-          const int f = NKA + ti * NK + kk;
-          qa[kk].hi = __builtin_bit_cast(bf16x8, kf[f * kWave + kslot(lane)]);
-          if constexpr (SPLIT) qa[kk].lo = __builtin_bit_cast(bf16x8, kf[(NKF + f) * kWave + kslot(lane)]);
+          if constexpr (SPLIT) {
+            const int f = NKA + ti * NK + kk;
+            qa[kk].hi = __builtin_bit_cast(bf16x8, kf[f * kWave + kslot(lane)]);
+            qa[kk].lo = __builtin_bit_cast(bf16x8, kf[(NKF + f) * kWave + kslot(lane)]);
+          } else {
+            qa[kk].hi = qt.frag(4 + ti, kk);
+          }
         }
         qm[ti] = zero4();
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) qm[ti] = mma_b<SPLIT>(m0[kk], qa[kk], qm[ti]);
       }
-      // P (split, six nonzero fragments) from global memory
-      const u32x4* pg = Pw + (static_cast<int64_t>(u.slot0 + ci) * hv + u.h) * (2 * kTFrags * kWave);
-      Frag pfr[kTFrags];
-#pragma unroll
-      for (int f = 0; f < kTFrags; ++f) {
-        pfr[f].hi = __builtin_bit_cast(bf16x8, pg[f * kWave + lane]);
-        pfr[f].lo = __builtin_bit_cast(bf16x8, pg[(kTFrags + f) * kWave + lane]);
-      }
+      if (TILES != kOutTiles) load_p();
       lds_barrier();   // Delta is in
       const f32x4* xdv = reinterpret_cast<const f32x4*>(xd);
       f32x4 D[4];
@@ -1122,26 +1266,23 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
         pout[ti] = mma_x3(dd0, pfr[tri_frag(ti, 0)], pout[ti]);
         if (ti >= 2) pout[ti] = mma_x3(dd1, pfr[tri_frag(ti, 1)], pout[ti]);
       }
-      if (!DMA_WAVE && prefetch) dma_half(ci + 1, b ^ 1, kHalf / 2, kHalf);
-    }
-    if (CL::kBuffers == 1) {
-      __syncthreads();   // every wave is done with the only buffer
-      if (ci + 1 < u.nch) {
-        if (dma_wave) dma_jobs(ci + 1, 0, J0{}, JN{});
-        else if (!DMA_WAVE && out_wave) dma_half(ci + 1, 0, 0, kHalf);
-      }
-    }
-    if (dma_wave || (!DMA_WAVE && out_wave)) wait_dma();
-    __syncthreads();     // next chunk's operands are in LDS; this buffer is free
-  }
-  if (out_wave) {
+      chunk_end(ci);
+    });
     if (u.nch > 0) store_chunk_out(o, u, u.nch - 1, hv, dv, colw, lane, pout);
-  } else if (chain_wave && state_out) {
-#pragma unroll
-    for (int td = 0; td < NT; ++td)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        state_out[sbase + static_cast<int64_t>(strow(td, lg, r)) * dv] = M[td][r];
+  } else {
+    wait_dma();
+    lds_barrier();
+    for (int ci = 0; ci < u.nch; ++ci) {
+      const bool prefetch = ci + 1 < u.nch;
+      lds_byte* other = lds_l + ((ci + 1) & 1) * L::kBytes;
+      if (prefetch) {
+        dma.template phase<3>(0, other);
+        dma.template phase<3>(1, other);
+      }
+      lds_barrier();   // mid-chunk
+      if (prefetch) dma.template phase<3>(2, other);
+      chunk_end(ci);
+    }
   }
 }
 
@@ -1157,10 +1298,9 @@ void k_scan_cols(const int32_t* __restrict__ cu, int32_t hk, int32_t hv, int32_t
     scan_cols_out_body<TIn, DK, TILES>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, qin, Kw, Tw,
                                        Sw, Pw, state_in, o, state_out);
   } else {
-    using L = ColsLds<TIn, DK, false>;
+    using L = ColsLds<TIn, DK>;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[L::kBuffers * L::kBytes];
-    scan_cols_body<TIn, DK, false>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, qin, Kw, Tw, Sw, Pw,
-                                   state_in, o, state_out);
+    scan_cols_body<TIn, DK>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, Kw, Tw, Sw, state_out);
   }
 }
 
@@ -1169,30 +1309,30 @@ void k_scan_cols(const int32_t* __restrict__ cu, int32_t hk, int32_t hv, int32_t
 // number of rounds): the forward of the sequences peeled off a whole-head
 // grid's partly empty last round, and of fp32 batches that do not fit on the
 // chip (see launch_scan).
-template <typename TIn, int DK>
-__global__ __launch_bounds__(cols_threads(true, sizeof(TIn) == 4)) __attribute__((amdgpu_waves_per_eu(1, 1)))
+template <typename TIn, int DK, int TILES>
+__global__ __launch_bounds__(cols_threads(true, sizeof(TIn) == 4, TILES))
+__attribute__((amdgpu_waves_per_eu(TILES == kOutTiles ? 2 : 1, TILES == kOutTiles ? 2 : 1)))
 void k_scan_cols_out_ord(const int32_t* __restrict__ cu, const SeqOrder order, int32_t hk, int32_t hv, int32_t dv,
                           const TIn* __restrict__ v, const TIn* __restrict__ kin, const TIn* __restrict__ qin,
                           const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                           const float* __restrict__ Sw, const u32x4* __restrict__ Pw,
                           const float* __restrict__ state_in, TIn* __restrict__ o, float* __restrict__ state_out) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[ColsOutLayout<TIn, DK>::kBytes];
-  scan_cols_out_body<TIn, DK>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, qin, Kw, Tw, Sw, Pw,
-                              state_in, o, state_out, &order);
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[ColsOutLayout<TIn, DK, TILES>::kBytes];
+  scan_cols_out_body<TIn, DK, TILES>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, qin, Kw, Tw, Sw,
+                                     Pw, state_in, o, state_out, &order);
 }
 
 // The wide column scan, tail replay only (grid N x Hv x d_v / COLS).
 template <typename TIn, int DK, int COLS>
 __global__ __launch_bounds__(cols_wide_threads(COLS)) __attribute__((amdgpu_waves_per_eu(COLS / 64, 2)))
 void k_scan_cols_wide(const int32_t* __restrict__ cu, const SeqOrder order, int32_t hk, int32_t hv, int32_t dv,
-                      const TIn* __restrict__ v, const TIn* __restrict__ kin, const TIn* __restrict__ qin,
+                      const TIn* __restrict__ v, const TIn* __restrict__ kin,
                       const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                       const float* __restrict__ Sw, float* __restrict__ state_out) {
-  using L = ColsLds<TIn, DK, false, COLS>;
+  using L = ColsLds<TIn, DK, COLS>;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[L::kBuffers * L::kBytes];
-  scan_cols_body<TIn, DK, false, COLS, kWhole, kWideTiles, false>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk,
-                                                                  hv, dv, v, kin, qin, Kw, Tw, Sw, nullptr,
-                                                                  nullptr, nullptr, state_out, SplitOut{}, &order);
+  scan_cols_body<TIn, DK, COLS, kWhole, kWideTiles, false>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v,
+                                                           kin, Kw, Tw, Sw, state_out, SplitOut{}, &order);
 }
 
 // Tail replay of bf16 inputs, 64 columns per workgroup: one 16-column tile per
@@ -1204,14 +1344,13 @@ void k_scan_cols_wide(const int32_t* __restrict__ cu, const SeqOrder order, int3
 template <typename TIn, int DK>
 __global__ __launch_bounds__((kSplitCols2 / 16 + 1) * kWave)
 void k_scan_cols_64(const int32_t* __restrict__ cu, const SeqOrder order, int32_t hk, int32_t hv, int32_t dv,
-                      const TIn* __restrict__ v, const TIn* __restrict__ kin, const TIn* __restrict__ qin,
+                      const TIn* __restrict__ v, const TIn* __restrict__ kin,
                       const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                       const float* __restrict__ Sw, float* __restrict__ state_out) {
-  using L = ColsLds<TIn, DK, false, kSplitCols2>;
+  using L = ColsLds<TIn, DK, kSplitCols2>;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[L::kBuffers * L::kBytes];
-  scan_cols_body<TIn, DK, false, kSplitCols2, kWhole, 1, true>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv,
-                                                               dv, v, kin, qin, Kw, Tw, Sw, nullptr, nullptr,
-                                                               nullptr, state_out, SplitOut{}, &order);
+  scan_cols_body<TIn, DK, kSplitCols2>((lds_byte*)lds, blockIdx.x, gridDim.x, cu, hk, hv, dv, v, kin, Kw, Tw, Sw,
+                                       state_out, SplitOut{}, &order);
 }
 
 // Tail replay in two halves, one launch: blocks [0, n_first) run the first
@@ -1224,23 +1363,22 @@ constexpr int cols_split_threads() { return (kSplitCols2 / 16 + 1) * kWave; }
 template <typename TIn, int DK>
 __global__ __launch_bounds__(cols_split_threads())
 void k_scan_cols_split(int32_t n_first, const int32_t* __restrict__ cu, int32_t hk, int32_t hv, int32_t dv,
-                       const TIn* __restrict__ v, const TIn* __restrict__ kin, const TIn* __restrict__ qin,
+                       const TIn* __restrict__ v, const TIn* __restrict__ kin,
                        const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                        const float* __restrict__ Sw, float* __restrict__ state_out, float* __restrict__ m2,
                        float* __restrict__ a2) {
-  using L1 = ColsLds<TIn, DK, false, kSplitCols1>;
-  using L2 = ColsLds<TIn, DK, false, kSplitCols2>;
+  using L1 = ColsLds<TIn, DK, kSplitCols1>;
+  using L2 = ColsLds<TIn, DK, kSplitCols2>;
   constexpr int kB1 = L1::kBuffers * L1::kBytes, kB2 = L2::kBuffers * L2::kBytes;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[kB1 > kB2 ? kB1 : kB2];
   const int b = blockIdx.x;
   if (b < n_first)
-    scan_cols_body<TIn, DK, false, kSplitCols1, kFirstHalf>((lds_byte*)lds, b, n_first, cu, hk, hv, dv, v, kin, qin,
-                                                            Kw, Tw, Sw, nullptr, nullptr, nullptr, state_out);
+    scan_cols_body<TIn, DK, kSplitCols1, kFirstHalf>((lds_byte*)lds, b, n_first, cu, hk, hv, dv, v, kin, Kw, Tw, Sw,
+                                                     state_out);
   else
-    scan_cols_body<TIn, DK, false, kSplitCols2, kSecondHalf>((lds_byte*)lds, b - n_first,
-                                                             static_cast<int>(gridDim.x) - n_first, cu, hk, hv, dv, v,
-                                                             kin, qin, Kw, Tw, Sw, nullptr, nullptr, nullptr, nullptr,
-                                                             SplitOut{m2, a2});
+    scan_cols_body<TIn, DK, kSplitCols2, kSecondHalf>((lds_byte*)lds, b - n_first,
+                                                      static_cast<int>(gridDim.x) - n_first, cu, hk, hv, dv, v, kin,
+                                                      Kw, Tw, Sw, nullptr, SplitOut{m2, a2});
 }
 
 // state = A state + B per (sequence, value head): A^T [d_k x d_k], state and
@@ -1368,15 +1506,14 @@ void k_scan_cols_intra(int32_t n_scan, const int32_t* __restrict__ cu_t, int32_t
                        const float* __restrict__ g_s, const float* __restrict__ beta_s, float scale,
                        u32x4* __restrict__ Kw_s, u32x4* __restrict__ Tw_s, float* __restrict__ Sw_s,
                        u32x4* __restrict__ Pw_s) {
-  using LS = ColsLds<TIn, DK, false>;
+  using LS = ColsLds<TIn, DK>;
   using LI = IntraLds<TIn, DK, true>;
   constexpr size_t kScanBytes = static_cast<size_t>(LS::kBuffers) * LS::kBytes;
   constexpr size_t kBytes = kScanBytes > sizeof(LI) ? kScanBytes : sizeof(LI);
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kBytes];
   if (static_cast<int>(blockIdx.x) < n_scan) {
-    scan_cols_body<TIn, DK, false>((lds_byte*)smem, blockIdx.x, n_scan, cu_t, hk, hv, dv, v_t, k_t, nullptr, Kw_t,
-                                   Tw_t,
-                                   Sw_t, nullptr, nullptr, nullptr, state_mid);
+    scan_cols_body<TIn, DK>((lds_byte*)smem, blockIdx.x, n_scan, cu_t, hk, hv, dv, v_t, k_t, Kw_t, Tw_t, Sw_t,
+                            state_mid);
   } else {
     const int i = blockIdx.x - n_scan;
     int slot, h;
@@ -1400,10 +1537,9 @@ void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t h
                  const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                  const float* __restrict__ Sw, const u32x4* __restrict__ Pw,
                  const float* __restrict__ state_in, TIn* __restrict__ o, float* __restrict__ state_out) {
-  using L = ScanLds<TIn, DK, DV, FWD, false>;
+  using L = ScanLds<TIn, DK, DV, FWD, true>;
   constexpr int NT = DK / 16;
   constexpr int W = DV / 16;
-  constexpr int PER_WAVE = (L::kJobs + W - 1) / W;   // DMA jobs per wave per chunk
   __shared__ __attribute__((aligned(1024))) unsigned char lds_g[L::kBuffers * L::kBytes];
   lds_byte* lds = (lds_byte*)lds_g;
   const int tid = threadIdx.x;
@@ -1413,16 +1549,8 @@ void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t h
   const int unit = xcd_cluster_remap(blockIdx.x, gridDim.x, hv / hk);
   const ScanUnit u = scan_unit(cu, unit / hv, unit % hv, hv, hk, &order);
   const int col = 16 * wave + lr;
-  const int64_t vrow = static_cast<int64_t>(hv) * DV;
-  // jobs wave + W * jj, jj in [j0, j1), of chunk ci into buffer b
-  auto dma_share = [&](int ci, int b, int j0, int j1) __attribute__((always_inline)) {
-    const ChunkSrc c = chunk_src<L>(u, ci, hk, hv, DV, 0, v, kin, qin, Kw, Tw, Sw, Pw);
-#pragma unroll
-    for (int jj = j0; jj < j1; ++jj) {
-      const int j = wave + W * jj;
-      if (j < L::kJobs) dma_job<L, TIn>(c, vrow, lds + b * L::kBytes, j, lane);
-    }
-  };
+  ChunkDma<L, TIn, W, FWD> dma;
+  dma.start(u, 0, wave, lane, hk, hv, DV, 0, v, kin, qin, Kw, Tw, Sw, Pw);
 
   f32x4 M[NT];
   Frag mb[DK / 32];
@@ -1431,33 +1559,28 @@ void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t h
   load_state<DK>(state_in, sbase, DV, lg, M, mb);
 
   if (u.nch > 0) {
-    dma_share(0, 0, 0, PER_WAVE);
+    dma.chunk(lds);
     wait_dma();
   }
   __syncthreads();
-  for (int ci = 0; ci < u.nch; ++ci) {
-    const int b = L::kBuffers == 2 ? (ci & 1) : 0;
+  each_chunk<L::kBuffers>(u.nch, [&](int ci, auto bc) __attribute__((always_inline)) {
+    constexpr int b = decltype(bc)::value;
     if constexpr (FWD) {
       if (ci > 0) store_chunk_out(o, u, ci - 1, hv, DV, col - lr, lane, pout);
     }
     const bool prefetch = L::kBuffers == 2 && ci + 1 < u.nch;
     // the next chunk's DMA share, a few jobs at the start of each region
     auto hook = [&](int k) __attribute__((always_inline)) {
-      if (prefetch) {
-        const int j0 = k * PER_WAVE / 7, j1 = (k + 1) * PER_WAVE / 7;
-        if (j1 > j0) dma_share(ci + 1, b ^ 1, j0, j1);
-      }
+      if (prefetch) dma.template phase<kDmaPhases>(k, lds + (b ^ 1) * L::kBytes);
     };
-    const u32x4* pg = FWD ? Pw + (static_cast<int64_t>(u.slot0 + ci) * hv + u.h) * (2 * kTFrags * kWave) : nullptr;
-    chunk_step<L, DK, FWD, false>((const unsigned char*)(lds + b * L::kBytes), 16 * wave, pg, lane, M, mb, pout,
-                                  hook);
+    chunk_step<L, DK, FWD, false>((const unsigned char*)(lds + b * L::kBytes), 16 * wave, lane, M, mb, pout, hook);
     if (L::kBuffers == 1) {
       __syncthreads();   // every wave is done with the only buffer
-      if (ci + 1 < u.nch) dma_share(ci + 1, 0, 0, PER_WAVE);
+      if (ci + 1 < u.nch) dma.chunk(lds);
     }
     wait_dma();          // this wave's share of the next chunk has landed
     __syncthreads();     // ... and everyone else's; this chunk's buffer is free
-  }
+  });
   if constexpr (FWD) {
     if (u.nch > 0) store_chunk_out(o, u, u.nch - 1, hv, DV, col - lr, lane, pout);
   }

@@ -240,6 +240,28 @@ def test_forward_batches_with_a_peeled_last_round(nseq, d):
         assert rel.item() <= 1e-3, f"sequence {i} (length {lens[i]})"
 
 
+@pytest.mark.parametrize("nseq,dk,dv", [(3, 128, 128), (4, 128, 128), (6, 64, 64), (20, 128, 64), (3, 64, 128)])
+def test_forward_batches_in_64_columns_bitwise(nseq, dk, dv):
+    # bf16 batches of 32 value heads whose 32-column grid does not fit on the
+    # chip but whose 64-column grid does (and every batch at d_v = 64, here 640
+    # workgroups in three rounds) run four recurrence and four output waves per
+    # workgroup; a single sequence runs one of each.  Same products, same order:
+    # states and outputs agree bit for bit, at the edges of a chunk too.
+    shape = synth.Shape(hk=16, hv=32, dk=dk, dv=dv, dtype="bf16")
+    lens = ([65, 1, 130, 0, 64, 63, 200] * 3)[:nseq]
+    seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
+    p = synth.pack(seqs)
+    x = device_inputs(p)
+    s0 = torch.randn(nseq, 32, dk, dv, generator=torch.Generator().manual_seed(5)).cuda()
+    o, st = gdn.chunk_forward(x["q"], x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"], state_in=s0)
+    for i in range(nseq):
+        xi = device_inputs(synth.pack([seqs[i]]))
+        oi, si = gdn.chunk_forward(xi["q"], xi["k"], xi["v"], xi["g"], xi["beta"], xi["cu"], xi["cu_host"],
+                                   state_in=s0[i:i + 1].contiguous())
+        assert torch.equal(st[i:i + 1], si), f"sequence {i} (length {lens[i]})"
+        assert torch.equal(o[int(p.cu_seqlens[i]):int(p.cu_seqlens[i + 1])], oi), f"sequence {i} (length {lens[i]})"
+
+
 def test_fp32_forward_beyond_the_chip_bitwise():
     # fp32 inputs with outputs: 72 varlen sequences x 4 heads need 1152
     # 32-column workgroups, more than the chip holds, and run in that form over
