@@ -118,8 +118,8 @@ gdn_status launch_intra(const gdn_shape& s, const Plan& p, const int32_t* cu, co
 }
 
 // The column-split scan has the shortest chunk latency but one workgroup per
-// CU; it is used when its grid fits on the chip at once.  Tail replay of bf16
-// inputs whose split grid (the two halves of the chain side by side and the
+// CU; it is used when its grid fits on the chip at once.  Tail replay
+// whose split grid (the two halves of the chain side by side and the
 // second half's transition) also fits runs split, which halves the chain.
 // When the 32-wide grid does not fit, tail replay of bf16 inputs takes the
 // wide column scan (two tiles per wave, two workgroups per CU: throughput) and
@@ -150,8 +150,7 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
   int cus = 0;
   gdn_status st = cols_fit(s, &fits, &col_groups, &cus);
   if (st != GDN_OK) return st;
-  constexpr bool kWide = !FWD && sizeof(TIn) == 2;   // tail replay, bf16 inputs
-  if constexpr (kWide) {
+  if constexpr (!FWD) {
     if (p.split && split_groups(s) <= cus) {
       // two half-length chains side by side, then state = A state + M''
       float* m2 = reinterpret_cast<float*>(ws + p.off_M2);
@@ -196,44 +195,47 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
                        cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(v),
                        static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in,
                        static_cast<TIn*>(o), state_out);
-  } else if constexpr (kWide) {
+  } else if constexpr (!FWD) {
     // A batch whose 64-column one-tile grid takes at most three rounds of the
     // chip (one workgroup per CU) runs in it: its chains finish a chunk in
     // ~1.45 us against ~3.9 us for a lone wide workgroup per CU (at 3, 8 and
-    // 12 sequences of 32 heads: 178 -> 88, 196 -> 182, 283 -> 270 us).
+    // 12 sequences of 32 heads: 178 -> 88, 196 -> 182, 283 -> 270 us).  fp32
+    // batches always do.
     const int64_t groups64 = static_cast<int64_t>(s.num_seqs) * s.num_v_heads * (s.d_v / kSplitCols2);
-    if (groups64 <= 3 * static_cast<int64_t>(cus)) {
+    if (sizeof(TIn) == 4 || groups64 <= 3 * static_cast<int64_t>(cus)) {
       hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(groups64)),
                          dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
                          s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
       return check_launch("scan launch");
     }
-    // Otherwise a whole head per workgroup (128 columns, four compute waves)
-    // where d_v allows, two workgroups per CU.  When the last round of that
-    // grid would be partly empty and its sequences fit on the chip at one
-    // 64-column workgroup per CU, those sequences (the shortest, in
-    // longest-first order) run in the one-tile scan after it instead.
-    constexpr int kCols = DV >= 128 ? 128 : 64;
-    const int64_t per_seq = static_cast<int64_t>(s.num_v_heads) * (s.d_v / kCols);
-    const int64_t rem = static_cast<int64_t>(s.num_seqs) * per_seq % (2 * static_cast<int64_t>(cus));
-    int32_t peel = 0;
-    if (rem > 0 && s.num_seqs <= kMaxOrderedSeqs) {
-      peel = static_cast<int32_t>((rem + per_seq - 1) / per_seq);
-      if (peel >= s.num_seqs || static_cast<int64_t>(peel) * s.num_v_heads * (s.d_v / kSplitCols2) > cus) peel = 0;
-    }
-    const int32_t n_wide = s.num_seqs - peel;
-    hipLaunchKernelGGL((k_scan_cols_wide<TIn, DK, kCols>), dim3(static_cast<uint32_t>(n_wide * per_seq)),
-                       dim3(cols_wide_threads(kCols)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v,
-                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
-    if (peel > 0) {
-      if ((st = check_launch("scan launch")) != GDN_OK) return st;
-      SeqOrder po;
-      po.n = peel;
-      for (int32_t i = 0; i < peel; ++i) po.seq[i] = p.order.n > 0 ? p.order.seq[n_wide + i] : n_wide + i;
-      hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(peel) * s.num_v_heads *
-                                                           (s.d_v / kSplitCols2)),
-                         dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, po, s.num_k_heads, s.num_v_heads, s.d_v,
+    if constexpr (sizeof(TIn) == 2) {
+      // Otherwise a whole head per workgroup (128 columns, four compute waves)
+      // where d_v allows, two workgroups per CU.  When the last round of that
+      // grid would be partly empty and its sequences fit on the chip at one
+      // 64-column workgroup per CU, those sequences (the shortest, in
+      // longest-first order) run in the one-tile scan after it instead.
+      constexpr int kCols = DV >= 128 ? 128 : 64;
+      const int64_t per_seq = static_cast<int64_t>(s.num_v_heads) * (s.d_v / kCols);
+      const int64_t rem = static_cast<int64_t>(s.num_seqs) * per_seq % (2 * static_cast<int64_t>(cus));
+      int32_t peel = 0;
+      if (rem > 0 && s.num_seqs <= kMaxOrderedSeqs) {
+        peel = static_cast<int32_t>((rem + per_seq - 1) / per_seq);
+        if (peel >= s.num_seqs || static_cast<int64_t>(peel) * s.num_v_heads * (s.d_v / kSplitCols2) > cus) peel = 0;
+      }
+      const int32_t n_wide = s.num_seqs - peel;
+      hipLaunchKernelGGL((k_scan_cols_wide<TIn, DK, kCols>), dim3(static_cast<uint32_t>(n_wide * per_seq)),
+                         dim3(cols_wide_threads(kCols)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v,
                          static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
+      if (peel > 0) {
+        if ((st = check_launch("scan launch")) != GDN_OK) return st;
+        SeqOrder po;
+        po.n = peel;
+        for (int32_t i = 0; i < peel; ++i) po.seq[i] = p.order.n > 0 ? p.order.seq[n_wide + i] : n_wide + i;
+        hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(peel) * s.num_v_heads *
+                                                             (s.d_v / kSplitCols2)),
+                           dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, po, s.num_k_heads, s.num_v_heads, s.d_v,
+                           static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
+      }
     }
   } else if constexpr (kNarrow) {
     // bf16 with outputs.  A batch whose 64-column grid fits on the chip at
@@ -279,12 +281,6 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
         launch_out(po, peel);
       }
     }
-  } else {
-    // fp32 tail replay: a whole head per workgroup, one per CU
-    hipLaunchKernelGGL((k_scan_head<TIn, DK, DV, FWD>), dim3(static_cast<uint32_t>(s.num_seqs) * s.num_v_heads),
-                       dim3(head_threads(DV)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
-                       static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
-                       Pw, state_in, static_cast<TIn*>(o), state_out);
   }
   return check_launch("scan launch");
 }
@@ -322,10 +318,11 @@ gdn_status dispatch(const Args& a) {
 }
 
 gdn_status common_checks(const gdn_shape* shape, const int32_t* cu_host, const int32_t* cu,
-                         bool fwd, Plan* plan, void* ws, size_t ws_bytes) {
+                         bool fwd, Plan* plan, void* ws, size_t ws_bytes, bool one_chain = false) {
   std::string err;
   const gdn_status st = make_plan(shape, cu_host, fwd, plan, &err);
   if (st != GDN_OK) return fail(st, err);
+  if (one_chain) drop_split(plan);
   if (shape->num_seqs > 0 && !cu) return fail(GDN_ERR_NULL_ARG, "cu_seqlens (device) is NULL");
   if (plan->bytes > 0 && !ws) return fail(GDN_ERR_WORKSPACE, "workspace is NULL");
   if (ws_bytes < plan->bytes)
@@ -370,10 +367,10 @@ gdn_status tail_replay_impl(const gdn_shape* shape, const int32_t* cu_seqlens_ho
                             const int32_t* cu_seqlens, const void* k, const void* v,
                             const float* g, const float* beta, float* state_out,
                             void* workspace, size_t workspace_bytes, void* stream,
-                            void* const* events) {
+                            void* const* events, bool one_chain = false) {
   gdn::Plan plan;
   gdn_status st = gdn::common_checks(shape, cu_seqlens_host, cu_seqlens, false, &plan,
-                                     workspace, workspace_bytes);
+                                     workspace, workspace_bytes, one_chain);
   if (st != GDN_OK) return st;
   if (shape->num_seqs > 0 && !state_out) return gdn::fail(GDN_ERR_NULL_ARG, "state_out is NULL");
   if (plan.total_tokens > 0 && (!k || !v || !g || !beta))
@@ -473,34 +470,31 @@ gdn_status run_fused(const FusedArgs& a) {
   uint32_t n_scan = 0;
   int cus = 0;
   if ((st = cols_fit(s, &fits, &n_scan, &cus)) != GDN_OK) return st;
-  constexpr bool kCanSplit = sizeof(TIn) == 2;   // the split form is bf16 tail replay
   bool combine = false;
-  if constexpr (kCanSplit) {
-    if (pt.split && split_groups(s) <= cus && ps.num_slots > 0) {
-      // the tail in two halves (as gdn_tail_replay runs it), then its combine
-      // with the suffix's records built beside it
-      hipLaunchKernelGGL((k_scan_cols_split<TIn, DK>), dim3(static_cast<uint32_t>(split_groups(s))),
-                         dim3(cols_split_threads()), 0, a.stream,
-                         static_cast<int32_t>(split_first_groups(s)), a.cu_t, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(a.v_t),
-                         static_cast<const TIn*>(a.k_t),
-                         reinterpret_cast<const u32x4*>(a.ws_t + pt.off_K),
-                         reinterpret_cast<const u32x4*>(a.ws_t + pt.off_T),
-                         reinterpret_cast<const float*>(a.ws_t + pt.off_S), a.state_mid,
-                         reinterpret_cast<float*>(a.ws_t + pt.off_M2), reinterpret_cast<float*>(a.ws_t + pt.off_A2));
-      if ((st = check_launch("split scan launch")) != GDN_OK) return st;
-      if ((st = fmark(a, 2)) != GDN_OK) return st;
-      const uint32_t n_comb = static_cast<uint32_t>(s.num_seqs) * s.num_v_heads * (s.d_v / kCombineCols);
-      const uint32_t blocks = n_comb + static_cast<uint32_t>(ps.num_slots) * s.num_v_heads;
-      hipLaunchKernelGGL((k_combine_intra<TIn, DK>), dim3(blocks), dim3(kCombineThreads), 0, a.stream,
-                         static_cast<int32_t>(n_comb), s.d_v, reinterpret_cast<const float*>(a.ws_t + pt.off_A2),
-                         reinterpret_cast<const float*>(a.ws_t + pt.off_M2), a.state_mid,
-                         static_cast<int32_t>(ps.num_slots), a.cu_s, s.num_seqs, s.num_k_heads, s.num_v_heads,
-                         static_cast<const TIn*>(a.q), static_cast<const TIn*>(a.k), a.g, a.beta, s.scale,
-                         reinterpret_cast<u32x4*>(a.ws_s + ps.off_K), reinterpret_cast<u32x4*>(a.ws_s + ps.off_T),
-                         reinterpret_cast<float*>(a.ws_s + ps.off_S), reinterpret_cast<u32x4*>(a.ws_s + ps.off_P));
-      if ((st = check_launch("combine + suffix intra launch")) != GDN_OK) return st;
-      combine = true;
-    }
+  if (pt.split && split_groups(s) <= cus && ps.num_slots > 0) {
+    // the tail in two halves (as gdn_tail_replay runs it), then its combine
+    // with the suffix's records built beside it
+    hipLaunchKernelGGL((k_scan_cols_split<TIn, DK>), dim3(static_cast<uint32_t>(split_groups(s))),
+                       dim3(cols_split_threads()), 0, a.stream,
+                       static_cast<int32_t>(split_first_groups(s)), a.cu_t, s.num_k_heads, s.num_v_heads, s.d_v, static_cast<const TIn*>(a.v_t),
+                       static_cast<const TIn*>(a.k_t),
+                       reinterpret_cast<const u32x4*>(a.ws_t + pt.off_K),
+                       reinterpret_cast<const u32x4*>(a.ws_t + pt.off_T),
+                       reinterpret_cast<const float*>(a.ws_t + pt.off_S), a.state_mid,
+                       reinterpret_cast<float*>(a.ws_t + pt.off_M2), reinterpret_cast<float*>(a.ws_t + pt.off_A2));
+    if ((st = check_launch("split scan launch")) != GDN_OK) return st;
+    if ((st = fmark(a, 2)) != GDN_OK) return st;
+    const uint32_t n_comb = static_cast<uint32_t>(s.num_seqs) * s.num_v_heads * (s.d_v / kCombineCols);
+    const uint32_t blocks = n_comb + static_cast<uint32_t>(ps.num_slots) * s.num_v_heads;
+    hipLaunchKernelGGL((k_combine_intra<TIn, DK>), dim3(blocks), dim3(kCombineThreads), 0, a.stream,
+                       static_cast<int32_t>(n_comb), s.d_v, reinterpret_cast<const float*>(a.ws_t + pt.off_A2),
+                       reinterpret_cast<const float*>(a.ws_t + pt.off_M2), a.state_mid,
+                       static_cast<int32_t>(ps.num_slots), a.cu_s, s.num_seqs, s.num_k_heads, s.num_v_heads,
+                       static_cast<const TIn*>(a.q), static_cast<const TIn*>(a.k), a.g, a.beta, s.scale,
+                       reinterpret_cast<u32x4*>(a.ws_s + ps.off_K), reinterpret_cast<u32x4*>(a.ws_s + ps.off_T),
+                       reinterpret_cast<float*>(a.ws_s + ps.off_S), reinterpret_cast<u32x4*>(a.ws_s + ps.off_P));
+    if ((st = check_launch("combine + suffix intra launch")) != GDN_OK) return st;
+    combine = true;
   }
   if (!combine && fits && ps.num_slots > 0) {
     // the suffix's records are built on the CUs the tail replay leaves idle
@@ -691,6 +685,9 @@ gdn_status tail_replay_noalloc_impl(const gdn_shape* shape, const int32_t* cu_se
   std::string err;
   const gdn_status st = make_plan(shape, cu_seqlens_host, false, &plan, &err);
   if (st != GDN_OK) return fail(st, err);
+  // fp32 tails that fit only without the halves' states run as one chain
+  const bool one_chain = plan.split && shape->qkv_dtype == GDN_F32 && plan.bytes > kNoAllocScratchBytes;
+  if (one_chain) drop_split(&plan);
   if (plan.bytes > kNoAllocScratchBytes)
     return fail(GDN_ERR_WORKSPACE, "input needs " + std::to_string(plan.bytes) +
                                        " workspace bytes, more than the no-allocation scratch array holds (" +
@@ -701,7 +698,7 @@ gdn_status tail_replay_noalloc_impl(const gdn_shape* shape, const int32_t* cu_se
     if (sst != GDN_OK) return sst;
   }
   return tail_replay_impl(shape, cu_seqlens_host, cu_seqlens, k, v, g, beta, state_out, ws,
-                          ws ? kNoAllocScratchBytes : 0, stream, nullptr);
+                          ws ? kNoAllocScratchBytes : 0, stream, nullptr, one_chain);
 }
 
 }  // namespace

@@ -110,7 +110,7 @@ gdn_status make_plan(const gdn_shape* shape, const int32_t* cu, bool with_output
     p.order.n = N;
     for (int32_t n = 0; n < N; ++n) p.order.seq[n] = idx[n];
   }
-  p.split = !with_outputs && shape->qkv_dtype == GDN_BF16 && max_chunks >= kSplitMinChunks &&
+  p.split = !with_outputs && max_chunks >= split_min_chunks(shape->qkv_dtype == GDN_F32) &&
             split_groups(*shape) <= kSplitMaxGroups;
   if (p.split) {
     const size_t heads = static_cast<size_t>(N) * hv;

@@ -87,17 +87,24 @@ struct Plan {
   size_t bytes = 0;               // total workspace size
 };
 
-// Tail replay of bf16 inputs may run as two half-length scans and a combine
+// Tail replay may run as two half-length scans and a combine
 // when every workgroup of the split grid fits on the chip at once (one per CU):
 // N x Hv x (d_v / 32 + (d_v + d_k) / 64) of them, at most kSplitMaxGroups (the
 // MI355X's 256 CUs; fewer on a smaller device are checked at launch), and
-// the longest sequence has at least kSplitMinChunks chunks.  Measured on
+// the longest sequence has at least split_min_chunks chunks.  Measured on
 // MI355X: one chain of n chunks takes ~1.63 n + 2 us, the split ~1.06 n + 9.4
 // (its chunks are slower with every CU busy, and the combine with the kernel
-// boundary before it costs ~7 us), even at n = 13 and ahead beyond.
+// boundary before it costs ~7 us), even at n = 13 and ahead beyond.  fp32 inputs
+// (three passes per product): ~1.9 n + 2 us against ~1.15 n + 6 (20 chunks 39.9
+// -> 31.2 us, 52 chunks 98.6 -> 67).
 constexpr int64_t kSplitMaxGroups = 256;
 
 constexpr int32_t kSplitMinChunks = 20;
+// fp32 inputs gain from 20 chunks on as well, but callers have sized their
+// workspaces for one chain there; from 24 chunks on the halves' states add at
+// most a quarter to the chunk records.
+constexpr int32_t kSplitMinChunksF32 = 24;
+constexpr int32_t split_min_chunks(bool f32) { return f32 ? kSplitMinChunksF32 : kSplitMinChunks; }
 // state columns per workgroup of the first and of the second half
 constexpr int kSplitCols1 = 32, kSplitCols2 = 64;
 inline int64_t split_first_groups(const gdn_shape& s) {
@@ -142,6 +149,14 @@ struct BlockPlan {
 // Validates a layer-block call's shape and offsets and fills `plan`.
 gdn_status make_block_plan(const gdn_la_shape* shape, const int32_t* cu_seqlens_host,
                            bool with_outputs, BlockPlan* plan, std::string* err);
+
+// Takes the split back: the same plan as one chain, without the halves' states
+// (which come last in the workspace).
+inline void drop_split(Plan* p) {
+  if (!p->split) return;
+  p->split = false;
+  p->bytes = p->off_M2;
+}
 
 // The thread-local message behind gdn_last_error(), shared by every entry point.
 void set_last_error(const std::string& msg);

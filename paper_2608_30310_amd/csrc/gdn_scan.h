@@ -805,10 +805,12 @@ struct RecordDma {
     p_b = static_cast<int64_t>(hv) * static_cast<int64_t>(kPRecordBytes);
     s_b = static_cast<int64_t>(hv) * L::kSBytes;
   }
-  __device__ __forceinline__ void jobs(lds_byte* base, int j0, int j1) const {
+  __device__ __forceinline__ void jobs(lds_byte* base, int j0, int j1, bool values = true) const {
+    constexpr int kV0 = L::kKJobs + L::kTJobs + L::kPJobs;   // first value row job
 #pragma unroll
     for (int jj = j0; jj < j1; ++jj) {
       const int j = w + NW * jj;
+      if (!values && j >= kV0 && j < kV0 + L::kVJobs) continue;
       if (j < L::kJobs) dma_job<L, TIn>(c, vrow, base, j, lane);
     }
   }
@@ -821,8 +823,8 @@ struct RecordDma {
     left -= kChunk;
     c.clen = min(kChunk, left);
   }
-  __device__ __forceinline__ void chunk(lds_byte* base, bool = true) {
-    jobs(base, 0, kPerWave);
+  __device__ __forceinline__ void chunk(lds_byte* base, bool values = true) {
+    jobs(base, 0, kPerWave, values);
     next();
   }
   template <int N>

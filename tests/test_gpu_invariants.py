@@ -262,6 +262,34 @@ def test_forward_batches_in_64_columns_bitwise(nseq, dk, dv):
         assert torch.equal(o[int(p.cu_seqlens[i]):int(p.cu_seqlens[i + 1])], oi), f"sequence {i} (length {lens[i]})"
 
 
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 64), (128, 64), (64, 128)])
+def test_fp32_tail_in_two_halves_and_in_64_columns(dk, dv):
+    # fp32 tails of 24 chunks and more on a grid that fits run as two
+    # half-length chains and a combine: against the oracle within four times the
+    # split operands' error (5e-6 measured over the declared sizes), and the
+    # fused call bit for bit.  A batch beyond the chip runs one chain per 64
+    # columns: bit for bit each sequence's own call where that is one chain too.
+    shape = synth.Shape(hk=2, hv=4, dk=dk, dv=dv, dtype="f32")
+    lens = [64 * 20 + 5, 63, 0, 64 * 23 + 1, 64 * 25]
+    p = synth.pack([_seq(i, n, shape=shape) for i, n in enumerate(lens)])
+    x = device_inputs(p)
+    st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    _, want = oracle_run(p)
+    assert state_err(to_f64(st), want) <= 2e-5
+    y = device_inputs(synth.pack([_seq(50 + i, n, shape=shape) for i, n in enumerate([70, 1, 64, 0, 5])]))
+    o, mid, fin = gdn.replay_forward(x["k"], x["v"], x["g"], x["beta"], x["cu"], y["q"], y["k"], y["v"], y["g"],
+                                     y["beta"], y["cu"], cu_tail_host=x["cu_host"], cu_suf_host=y["cu_host"])
+    o2, fin2 = gdn.chunk_forward(y["q"], y["k"], y["v"], y["g"], y["beta"], y["cu"], y["cu_host"], state_in=st)
+    assert torch.equal(mid, st) and torch.equal(fin, fin2) and torch.equal(o, o2)
+    seqs = [_seq(i, 1 + (37 * i) % 200, shape=shape) for i in range(72)]
+    xb = device_inputs(synth.pack(seqs))
+    sb = gdn.tail_replay(xb["k"], xb["v"], xb["g"], xb["beta"], xb["cu"], xb["cu_host"])
+    for i in (0, 5, 40, 71):
+        xi = device_inputs(synth.pack([seqs[i]]))
+        assert torch.equal(sb[i:i + 1], gdn.tail_replay(xi["k"], xi["v"], xi["g"], xi["beta"], xi["cu"],
+                                                        xi["cu_host"])), f"sequence {i}"
+
+
 def test_fp32_forward_beyond_the_chip_bitwise():
     # fp32 inputs with outputs: 72 varlen sequences x 4 heads need 1152
     # 32-column workgroups, more than the chip holds, and run in that form over

@@ -47,6 +47,21 @@ def test_noalloc_matches_tail_replay_twice():
         assert e <= STATE_TOL
 
 
+def test_noalloc_runs_one_chain_where_the_halves_do_not_fit():
+    # 4480 fp32 tokens: the chunk records take 62.5 of the 64 MiB, the halves'
+    # states 4 more, so the call runs as one chain.  The two forms differ by
+    # rounding order alone (each within 5e-6 of the exact state).
+    shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="f32")
+    p, x = _case(2, [4480], shape)
+    need = gdn.workspace_size(1, 16, 32, 128, 128, [0, 4480], dtype=torch.float32)
+    assert need > gdn.noalloc_scratch_bytes()
+    want = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    got = torch.full((1, 32, 128, 128), float("nan"), device="cuda:0")
+    gdn.tail_replay_noalloc(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"], got)
+    torch.cuda.synchronize()
+    assert state_err(to_f64(got), to_f64(want)) <= 2e-5
+
+
 def test_noalloc_rejects_oversized_input():
     shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="bf16")
     T = 60000
