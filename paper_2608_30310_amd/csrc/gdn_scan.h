@@ -50,6 +50,12 @@ __device__ __forceinline__ void dma16(const void* src, lds_byte* dst) {
 }
 
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// The same, but for the N youngest.
+template <int N>
+__device__ __forceinline__ void wait_dma_but() {
+  static_assert(N < 64, "vmcnt holds six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 // The same from `base + off`: a uniform base and a 32-bit lane offset, so the
 // load takes the scalar-base form and its address costs no 64-bit lane
@@ -614,15 +620,56 @@ __device__ __forceinline__ void chunk_step_tiles(const unsigned char* base, int 
 }
 
 // f(j, b) for chunks j = 0 .. n - 1, b (a compile-time constant) the LDS buffer
-// of chunk j.  With two buffers the loop takes two chunks a turn, so every LDS
-// address of a chunk is a lane address that never changes plus a constant.
+// of chunk j.  The loop takes as many chunks a turn as there are buffers, so
+// every LDS address of a chunk is a lane address that never changes plus a
+// constant.
 template <int BUFFERS, typename F>
 __device__ __forceinline__ void each_chunk(int n, F&& f) {
   for (int j = 0; j < n; j += BUFFERS) {
     f(j, std::integral_constant<int, 0>{});
-    if constexpr (BUFFERS == 2) {
+    if constexpr (BUFFERS > 1) {
       if (j + 1 < n) f(j + 1, std::integral_constant<int, 1>{});
     }
+    if constexpr (BUFFERS > 2) {
+      if (j + 2 < n) f(j + 2, std::integral_constant<int, 2>{});
+    }
+  }
+}
+
+// The loop of the DMA wave beside output waves, over chunks 0 .. n - 1 into a
+// ring of RING buffers.
+// With three buffers and a long chain it runs two chunks ahead, so a chunk's
+// operands have two chunks' time to arrive: over 32768 tokens, whose records
+// and inputs come from HBM, the forward scan takes 750 us so and 900 one chunk
+// ahead.  A short chain stays one ahead: its first chunk then waits for its own
+// operands alone (16 chunks 27.5 against 28.5 us).  The barriers are those of
+// the recurrence and output waves' loops.
+constexpr int kFarChunks = 32;
+template <int RING, typename D>
+__device__ __forceinline__ void dma_ring(D& dma, lds_byte* lds, int buf_bytes, int n) {
+  static_assert(RING == 2 || RING == 3, "one or two chunks ahead");
+  const int ahead = RING == 3 && n >= kFarChunks ? 2 : 1;
+  int b = 0;
+  // the next chunk's DMA, while the compute waves work on the other buffers
+  auto issue = [&]() __attribute__((always_inline)) {
+    dma.chunk(lds + b * buf_bytes);
+    b = b + 1 == RING ? 0 : b + 1;
+  };
+  // the next chunk's has landed, the youngest, a further one's, may be under way
+  auto wait_next = [&](bool further) __attribute__((always_inline)) {
+    if (further) wait_dma_but<D::kPerWave>();
+    else wait_dma();
+  };
+  if (n > 0) issue();
+  if (ahead == 2) issue();
+  wait_next(ahead == 2);
+  lds_barrier();
+  for (int j = 0; j < n; ++j) {
+    const bool more = j + ahead < n;
+    if (more) issue();
+    lds_barrier();   // mid-chunk
+    wait_next(more && ahead == 2);
+    lds_barrier();   // the next chunk's operands are in LDS; this chunk's buffer is free
   }
 }
 
@@ -950,6 +997,7 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
                                                float* __restrict__ state_out, SplitOut split = {},
                                                const SeqOrder* order = nullptr) {
   using L = ColsLds<TIn, DK, COLS>;
+  static_assert(L::kBuffers == 2, "the next chunk's DMA runs beside a chunk");
   constexpr bool SPLIT = PART != kWhole;
   constexpr int NT = DK / 16;
   constexpr int CW = COLS / (16 * NC);   // compute waves
@@ -1003,8 +1051,8 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
   }
   const int nch = ce - cb;
   // The data waves and the compute waves run loops of their own with the same
-  // barriers (two per chunk with one buffer, else one), so the state lives in
-  // the compute waves' loop alone.
+  // barriers (one before the first chunk and one per chunk), so the state lives
+  // in the compute waves' loop alone.
   if (data_wave) {
     if (dma_wave && nch > 0) {
       dma.chunk(lds_l, !ident);
@@ -1057,7 +1105,7 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
     const unsigned char* buf = (const unsigned char*)(lds_l + b * L::kBytes);
     if constexpr (NC > 1) {
       // without a DMA wave: the next chunk's share, spread over the phases
-      const bool prefetch = !DMA_WAVE && L::kBuffers == 2 && j + 1 < nch;
+      const bool prefetch = !DMA_WAVE && j + 1 < nch;
       chunk_step_tiles<L, DK, NC>(buf, 16 * NC * wave, lane, M, mb, [&](int p) __attribute__((always_inline)) {
         if constexpr (!DMA_WAVE) {
           if (prefetch) dma.template phase<kDmaPhases>(p, lds_l + (b ^ 1) * L::kBytes);
@@ -1067,13 +1115,6 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
     } else {
       f32x4 none[4];
       chunk_step<L, DK, false, false>(buf, 16 * wave, lane, M[0], mb[0], none, [](int) {});
-    }
-    if (L::kBuffers == 1) {
-      __syncthreads();   // done with the only buffer
-      if (!DMA_WAVE && j + 1 < nch) {
-        dma.chunk(lds_l, !ident);
-        wait_dma();
-      }
     }
     __syncthreads();     // next chunk's operands are in LDS (every wave's share)
   });
@@ -1104,7 +1145,8 @@ struct ColsOutLayout {
   static constexpr int kDBytes = 4 * kWave * 16;
   static constexpr int kMBytes = DK / 32 * 2 * kWave * 16;
   static constexpr int kTileBytes = kDBytes + kMBytes;
-  static constexpr int kBuffers = 2 * L::kBytes + TILES * kTileBytes <= kLdsBytes ? 2 : 1;
+  static constexpr int fits(int n) { return n * L::kBytes + TILES * kTileBytes <= kLdsBytes; }
+  static constexpr int kBuffers = cols_dma_waves(L::kSplit, TILES) > 0 && fits(3) ? 3 : fits(2) ? 2 : 1;
   static constexpr int kOffX = kBuffers * L::kBytes;
   static constexpr int kBytes = kOffX + TILES * kTileBytes;
   static_assert(kBytes <= kLdsBytes, "column scan with outputs does not fit in LDS");
@@ -1136,7 +1178,10 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
   constexpr int NKA = ka_frags(DK);
   constexpr int NKF = L::kKFrags;
   constexpr int DW = cols_dma_waves(SPLIT, TILES);
-  constexpr bool TWO = CL::kBuffers == 2;
+  constexpr bool TWO = CL::kBuffers > 1;
+  // output waves that issue DMA store a chunk's outputs after it, in the next
+  // chunk; others at once (32768 tokens: 900 -> 855 us before the third buffer)
+  constexpr bool kDefer = TILES == kOutTiles;
   static_assert(TILES == 2 || !SPLIT, "fp32 inputs: two tiles per workgroup");
   static_assert(TWO || DW == 0, "a DMA wave fills the other buffer");
   const int tid = threadIdx.x;
@@ -1161,7 +1206,7 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
   if (issues) dma.start(u, 0, tile, lane, hk, hv, dv, col0, v, kin, qin, Kw, Tw, Sw, Pw);
 
   // each role runs a loop of its own with the same barriers
-  if (issues && u.nch > 0) dma.chunk(lds_l);
+  if (DW == 0 && issues && u.nch > 0) dma.chunk(lds_l);
   auto chunk_end = [&](int ci) __attribute__((always_inline)) {
     if (!TWO) {
       lds_barrier();   // every wave is done with the only buffer
@@ -1216,12 +1261,10 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
           pfr[f].lo = __builtin_bit_cast(bf16x8, pg[(kTFrags + f) * kWave + lane]);
         }
       };
-      if (TILES == kOutTiles) {
-        load_p();
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      load_p();
+      __builtin_amdgcn_sched_barrier(0);
       if (DW == 0 && TWO && ci + 1 < u.nch) dma.chunk(lds_l + (b ^ 1) * L::kBytes);
-      if (ci > 0) store_chunk_out(o, u, ci - 1, hv, dv, colw, lane, pout);
+      if (kDefer && ci > 0) store_chunk_out(o, u, ci - 1, hv, dv, colw, lane, pout);
       // (Q M0)^T: A = split M0 from the recurrence wave, B = Q fragments
       const u32x4* kf = reinterpret_cast<const u32x4*>(base + L::kOffK);
       const KeyTile<DK> qt{base + L::kOffK, lane};
@@ -1251,7 +1294,6 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) qm[ti] = mma_b<SPLIT>(m0[kk], qa[kk], qm[ti]);
       }
-      if (TILES != kOutTiles) load_p();
       lds_barrier();   // Delta is in
       const f32x4* xdv = reinterpret_cast<const f32x4*>(xd);
       f32x4 D[4];
@@ -1268,23 +1310,12 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
         pout[ti] = mma_x3(dd0, pfr[tri_frag(ti, 0)], pout[ti]);
         if (ti >= 2) pout[ti] = mma_x3(dd1, pfr[tri_frag(ti, 1)], pout[ti]);
       }
+      if (!kDefer) store_chunk_out(o, u, ci, hv, dv, colw, lane, pout);
       chunk_end(ci);
     });
-    if (u.nch > 0) store_chunk_out(o, u, u.nch - 1, hv, dv, colw, lane, pout);
-  } else {
-    wait_dma();
-    lds_barrier();
-    for (int ci = 0; ci < u.nch; ++ci) {
-      const bool prefetch = ci + 1 < u.nch;
-      lds_byte* other = lds_l + ((ci + 1) & 1) * L::kBytes;
-      if (prefetch) {
-        dma.template phase<3>(0, other);
-        dma.template phase<3>(1, other);
-      }
-      lds_barrier();   // mid-chunk
-      if (prefetch) dma.template phase<3>(2, other);
-      chunk_end(ci);
-    }
+    if (kDefer && u.nch > 0) store_chunk_out(o, u, u.nch - 1, hv, dv, colw, lane, pout);
+  } else if constexpr (DW > 0) {
+    dma_ring<CL::kBuffers>(dma, lds_l, L::kBytes, u.nch);
   }
 }
 
@@ -1565,8 +1596,8 @@ void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t h
     wait_dma();
   }
   __syncthreads();
-  each_chunk<L::kBuffers>(u.nch, [&](int ci, auto bc) __attribute__((always_inline)) {
-    constexpr int b = decltype(bc)::value;
+  for (int ci = 0; ci < u.nch; ++ci) {
+    const int b = L::kBuffers == 2 ? (ci & 1) : 0;
     if constexpr (FWD) {
       if (ci > 0) store_chunk_out(o, u, ci - 1, hv, DV, col - lr, lane, pout);
     }
@@ -1582,7 +1613,7 @@ void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t h
     }
     wait_dma();          // this wave's share of the next chunk has landed
     __syncthreads();     // ... and everyone else's; this chunk's buffer is free
-  });
+  }
   if constexpr (FWD) {
     if (u.nch > 0) store_chunk_out(o, u, u.nch - 1, hv, DV, col - lr, lane, pout);
   }
