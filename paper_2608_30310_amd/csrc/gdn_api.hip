@@ -196,13 +196,12 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
                        static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in,
                        static_cast<TIn*>(o), state_out);
   } else if constexpr (!FWD) {
-    // A batch whose 64-column one-tile grid takes at most three rounds of the
-    // chip (one workgroup per CU) runs in it: its chains finish a chunk in
-    // ~1.45 us against ~3.9 us for a lone wide workgroup per CU (at 3, 8 and
-    // 12 sequences of 32 heads: 178 -> 88, 196 -> 182, 283 -> 270 us).  fp32
-    // batches always do.
+    // One 16-column tile per wave, 64 columns per workgroup: fp32 batches, those
+    // whose grid fits on the chip so (3 sequences of 32 heads: 178 -> 88 us
+    // against the wide scan), and those for which the plan prefers it (see
+    // Plan::wide_tail).
     const int64_t groups64 = static_cast<int64_t>(s.num_seqs) * s.num_v_heads * (s.d_v / kSplitCols2);
-    if (sizeof(TIn) == 4 || groups64 <= 3 * static_cast<int64_t>(cus)) {
+    if (sizeof(TIn) == 4 || groups64 <= cus || !p.wide_tail) {
       hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(groups64)),
                          dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
                          s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);

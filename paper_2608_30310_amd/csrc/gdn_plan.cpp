@@ -110,6 +110,21 @@ gdn_status make_plan(const gdn_shape* shape, const int32_t* cu, bool with_output
     p.order.n = N;
     for (int32_t n = 0; n < N; ++n) p.order.seq[n] = idx[n];
   }
+  if (!with_outputs && N <= kMaxOrderedSeqs) {
+    // chunk count of the sequence of rank r, longest first
+    auto ranked = [&](int64_t r) -> int64_t {
+      if (r >= N) return 0;
+      const int32_t n = p.order.n > 0 ? p.order.seq[r] : static_cast<int32_t>(r);
+      return (static_cast<int64_t>(cu[n + 1]) - cu[n] + kChunk - 1) / kChunk;
+    };
+    const int64_t per_round = kSplitMaxGroups / (static_cast<int64_t>(hv) * (shape->d_v / 64));
+    const int64_t resident = 2 * kSplitMaxGroups / hv / (shape->d_v == 64 ? 1 : 2);
+    if (per_round > 0) {
+      int64_t steps = 0;
+      for (int64_t r = 0; r < N; r += per_round) steps += ranked(r);
+      p.wide_tail = steps > 1.7 * static_cast<double>(ranked(0)) + static_cast<double>(ranked(resident));
+    }
+  }
   p.split = !with_outputs && max_chunks >= split_min_chunks(shape->qkv_dtype == GDN_F32) &&
             split_groups(*shape) <= kSplitMaxGroups;
   if (p.split) {

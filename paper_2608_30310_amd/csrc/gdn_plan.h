@@ -79,6 +79,17 @@ struct Plan {
   // Longest-first order of the sequences, for scans whose grid exceeds the
   // chip (passed by value in the kernel's arguments)
   SeqOrder order;
+  // Tail replay of bf16 batches beyond the chip: two tiles per wave (the wide
+  // scan, all of whose workgroups are resident from the start) rather than one
+  // tile per wave in rounds of 64-column workgroups.  In units of the latter's
+  // chunk time (~1.55 us) the rounds take the sum of each round's longest
+  // chain, the wide scan ~1.7 x the longest chain (alone on its CU, ~2.9 us a
+  // chunk) plus the longest chain that shares a CU.  Measured at 32 heads, d =
+  // 128: 5, 8 and 12 chains of 32 chunks 101, 108 and 157 us in rounds, 93, 99
+  // and 151 wide; 6 and 8 ragged ones (52 against 91 and 83 against 102 steps)
+  // 73 and 120 against 115 and 135; 12 and 16 ragged ones 150 and 186 against
+  // 137 and 169.
+  bool wide_tail = true;
   // Tail replay in two halves (see split_groups): the second half's state
   // from zero and its transition, fp32
   bool split = false;

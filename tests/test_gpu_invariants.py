@@ -212,6 +212,24 @@ def test_one_tile_and_wide_batches_bitwise(nseq):
         assert torch.equal(st[i:i + 1], sti), f"sequence {i} (length {lens[i]})"
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens", [[200] * 9, [1200, 1] + [70, 0, 64, 65, 10, 3, 1], [700, 650] + [300] * 15 + [0]],
+                         ids=["even", "one_long", "two_per_cu"])
+def test_tail_batches_in_rounds_and_all_resident_bitwise(lens, d):
+    # 32 value heads beyond the chip: even batches run two tiles per wave with
+    # every workgroup resident from the start, batches with one long chain in
+    # rounds of 64-column workgroups.  States agree bit for bit with each
+    # sequence's own call (below 20 chunks: one chain) either way.
+    shape = synth.Shape(hk=16, hv=32, dk=d, dv=d, dtype="bf16")
+    seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
+    x = device_inputs(synth.pack(seqs))
+    st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    for i, n in enumerate(lens):
+        xi = device_inputs(synth.pack([seqs[i]]))
+        sti = gdn.tail_replay(xi["k"], xi["v"], xi["g"], xi["beta"], xi["cu"], xi["cu_host"])
+        assert torch.equal(st[i:i + 1], sti), f"sequence {i} (length {n})"
+
+
 @pytest.mark.parametrize("nseq,d", [(12, 128), (36, 128), (12, 64)])
 def test_forward_batches_with_a_peeled_last_round(nseq, d):
     # 12 and 36 sequences at 32 value heads run the forward on the whole-head
