@@ -91,7 +91,7 @@ gdn_status gdn_workspace_size(const gdn_shape* shape,
  *   k [T,Hk,d_k], v [T,Hv,d_v] (qkv_dtype); g, beta [T,Hv] fp32.
  * workspace: device memory of at least gdn_workspace_size(..., 0) bytes,
  * 256-byte aligned; its contents on entry do not matter.
- * For bf16 inputs whose longest tail has at least 20 chunks and whose batch
+ * Where the longest tail has at least 20 chunks (fp32 inputs: 24) and the batch
  * is small enough (N x Hv x (d_v / 32 + (d_v + d_k) / 64) workgroups fit on
  * the device at once), the chain is evaluated in two halves: the state is
  * linear in the first half's state, so it is formed as the second half's
