@@ -163,8 +163,8 @@ __device__ __forceinline__ int kslot_inv(int p) { return (p & 48) | ((p + 16 - 4
 // a row, with the 16-byte pieces of row r at positions piece ^ row_swz(r).
 // Whole rows are what the DMA fetches best: 1 KiB as 4 rows of 256 bytes keeps
 // the CU's vector memory path busy for 34 clocks, as the 16 rows x 64 bytes of
-// an operand fragment for 78 (measured at a row stride of 64 KiB).  With the
-// swizzle a 16-byte operand read, which takes lanes {0-3, 12-15, 20-23, 24-27},
+// an operand fragment for 78 (row stride 64 KiB, four waves, launch durations
+// taken at 2.2 GHz).  With the swizzle a 16-byte operand read, which takes lanes {0-3, 12-15, 20-23, 24-27},
 // {4-7, 8-11, 16-19, 28-31} (and the same of the upper half) at a time, is free
 // of bank conflicts, and a transposing 8-byte read, 32 consecutive lanes at a
 // time, meets each bank twice, the least there is (its lanes all want the same
