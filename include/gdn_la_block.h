@@ -100,7 +100,9 @@ gdn_status gdn_la_block_workspace_size(const gdn_la_shape* shape,
  * not NULL, steps 5-7 also write the layer output [T, D] (the next layer's
  * input); when it is NULL (a group's last layer) the query, z and output
  * paths are skipped and the in-projection computes only the k, v, a, b rows.
- * workspace: at least gdn_la_block_workspace_size(..., out != NULL) bytes.
+ * workspace: at least gdn_la_block_workspace_size(..., out != NULL) bytes; fp32
+ * intermediates without outputs may lack the halves' states, as in
+ * gdn_tail_replay.
  */
 gdn_status gdn_la_block_replay(const gdn_la_shape* shape, const gdn_la_weights* weights,
                                const int32_t* cu_seqlens_host, const int32_t* cu_seqlens,

@@ -98,6 +98,9 @@ gdn_status gdn_workspace_size(const gdn_shape* shape,
  * transition applied to the first half's state plus the second half's state
  * from zero.  The result equals the one-chain evaluation up to rounding order
  * (about 1e-6 relative); below those sizes it is the one-chain evaluation.
+ * For fp32 inputs the last N x Hv x d_k x (d_v + d_k) x 4 bytes, the halves'
+ * states, may be missing from the workspace: the call then evaluates one chain.
+ * bf16 inputs need all of gdn_workspace_size(..., 0).
  */
 gdn_status gdn_tail_replay(const gdn_shape* shape,
                            const int32_t* cu_seqlens_host,
@@ -181,7 +184,8 @@ const char* gdn_stage_name(int32_t with_outputs, int32_t stage);
  *   o [Ts,Hv,d_v]: suffix outputs; state_out: final state (NULL = not
  *   written; may equal state_mid, must not otherwise overlap it).
  * workspace: at least gdn_replay_forward_workspace_size(...) bytes, 256-byte
- * aligned.  Validation and errors as for the two separate calls.
+ * aligned (fp32 inputs: less the halves' states, as in gdn_tail_replay).
+ * Validation and errors as for the two separate calls.
  */
 gdn_status gdn_replay_forward_workspace_size(const gdn_shape* shape,
                                              const int32_t* cu_tail_host,
@@ -238,12 +242,15 @@ gdn_status gdn_decode_step(const gdn_shape* shape,
  * Tail replay that allocates nothing, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same operation, arguments, layouts and results as
- * gdn_tail_replay (the same kernels, so the states are bit for bit equal),
- * but the workspace is a device array inside the library of
- * GDN_NOALLOC_SCRATCH_BYTES bytes, one copy per GPU, held until the process
- * ends; the caller still owns k, v, g, beta and state_out.  Inputs whose
- * workspace (gdn_workspace_size(..., 0, ...)) exceeds the array are rejected
- * with GDN_ERR_WORKSPACE before anything is enqueued.  The array's device
+ * gdn_tail_replay with a workspace of GDN_NOALLOC_SCRATCH_BYTES bytes (the same
+ * kernels, so the states are bit for bit equal), but the workspace is a device
+ * array inside the library, one copy per GPU, held until the process ends; the
+ * caller still owns k, v, g, beta and state_out.  Inputs that this size is not
+ * enough for are rejected with GDN_ERR_WORKSPACE before anything is enqueued:
+ * bf16 inputs whose gdn_workspace_size(..., 0) exceeds it, and fp32 inputs where
+ * the chunk records alone do (between the two, fp32 inputs run as one chain, see
+ * gdn_tail_replay, so the states differ by rounding order from those of a call
+ * with a full workspace).  The array's device
  * address is looked up on the first call on each device (the current device
  * at the call); no call allocates, frees or synchronises.  Every call on one
  * GPU shares that GPU's array: calls that may overlap on one GPU (on

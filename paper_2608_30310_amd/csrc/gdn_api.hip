@@ -317,11 +317,11 @@ gdn_status dispatch(const Args& a) {
 }
 
 gdn_status common_checks(const gdn_shape* shape, const int32_t* cu_host, const int32_t* cu,
-                         bool fwd, Plan* plan, void* ws, size_t ws_bytes, bool one_chain = false) {
+                         bool fwd, Plan* plan, void* ws, size_t ws_bytes) {
   std::string err;
   const gdn_status st = make_plan(shape, cu_host, fwd, plan, &err);
   if (st != GDN_OK) return fail(st, err);
-  if (one_chain) drop_split(plan);
+  fit_split(*shape, ws_bytes, plan);
   if (shape->num_seqs > 0 && !cu) return fail(GDN_ERR_NULL_ARG, "cu_seqlens (device) is NULL");
   if (plan->bytes > 0 && !ws) return fail(GDN_ERR_WORKSPACE, "workspace is NULL");
   if (ws_bytes < plan->bytes)
@@ -366,10 +366,10 @@ gdn_status tail_replay_impl(const gdn_shape* shape, const int32_t* cu_seqlens_ho
                             const int32_t* cu_seqlens, const void* k, const void* v,
                             const float* g, const float* beta, float* state_out,
                             void* workspace, size_t workspace_bytes, void* stream,
-                            void* const* events, bool one_chain = false) {
+                            void* const* events) {
   gdn::Plan plan;
   gdn_status st = gdn::common_checks(shape, cu_seqlens_host, cu_seqlens, false, &plan,
-                                     workspace, workspace_bytes, one_chain);
+                                     workspace, workspace_bytes);
   if (st != GDN_OK) return st;
   if (shape->num_seqs > 0 && !state_out) return gdn::fail(GDN_ERR_NULL_ARG, "state_out is NULL");
   if (plan.total_tokens > 0 && (!k || !v || !g || !beta))
@@ -530,12 +530,14 @@ gdn_status fused_dtype(const FusedArgs& a) {
   return a.s->qkv_dtype == GDN_BF16 ? run_fused<uint16_t, DK, DV>(a) : run_fused<float, DK, DV>(a);
 }
 
+// The tail's and the suffix's plans for a workspace of `have` bytes.
 gdn_status fused_plans(const gdn_shape* shape, const int32_t* cu_tail_host, const int32_t* cu_suf_host,
-                       Plan* pt, Plan* ps, size_t* off_s, size_t* bytes) {
+                       size_t have, Plan* pt, Plan* ps, size_t* off_s, size_t* bytes) {
   std::string err;
   gdn_status st = make_plan(shape, cu_tail_host, false, pt, &err);
   if (st != GDN_OK) return fail(st, "tail: " + err);
   if ((st = make_plan(shape, cu_suf_host, true, ps, &err)) != GDN_OK) return fail(st, "suffix: " + err);
+  fit_split(*shape, have > ps->bytes ? have - ps->bytes : 0, pt);   // plan sizes are multiples of kAlign
   *off_s = (pt->bytes + kAlign - 1) / kAlign * kAlign;
   *bytes = *off_s + ps->bytes;
   return GDN_OK;
@@ -549,7 +551,7 @@ gdn_status replay_forward_impl(const gdn_shape* shape, const int32_t* cu_tail_ho
                                void* workspace, size_t workspace_bytes, void* stream, void* const* events) {
   Plan pt, ps;
   size_t off_s = 0, bytes = 0;
-  gdn_status st = fused_plans(shape, cu_tail_host, cu_suf_host, &pt, &ps, &off_s, &bytes);
+  gdn_status st = fused_plans(shape, cu_tail_host, cu_suf_host, workspace_bytes, &pt, &ps, &off_s, &bytes);
   if (st != GDN_OK) return st;
   if (shape->num_seqs > 0 && (!cu_tail || !cu_suf)) return fail(GDN_ERR_NULL_ARG, "cu_seqlens (device) is NULL");
   if (bytes > 0 && !workspace) return fail(GDN_ERR_WORKSPACE, "workspace is NULL");
@@ -685,8 +687,7 @@ gdn_status tail_replay_noalloc_impl(const gdn_shape* shape, const int32_t* cu_se
   const gdn_status st = make_plan(shape, cu_seqlens_host, false, &plan, &err);
   if (st != GDN_OK) return fail(st, err);
   // fp32 tails that fit only without the halves' states run as one chain
-  const bool one_chain = plan.split && shape->qkv_dtype == GDN_F32 && plan.bytes > kNoAllocScratchBytes;
-  if (one_chain) drop_split(&plan);
+  fit_split(*shape, kNoAllocScratchBytes, &plan);
   if (plan.bytes > kNoAllocScratchBytes)
     return fail(GDN_ERR_WORKSPACE, "input needs " + std::to_string(plan.bytes) +
                                        " workspace bytes, more than the no-allocation scratch array holds (" +
@@ -697,7 +698,7 @@ gdn_status tail_replay_noalloc_impl(const gdn_shape* shape, const int32_t* cu_se
     if (sst != GDN_OK) return sst;
   }
   return tail_replay_impl(shape, cu_seqlens_host, cu_seqlens, k, v, g, beta, state_out, ws,
-                          ws ? kNoAllocScratchBytes : 0, stream, nullptr, one_chain);
+                          ws ? kNoAllocScratchBytes : 0, stream, nullptr);
 }
 
 }  // namespace
@@ -760,7 +761,7 @@ gdn_status gdn_replay_forward_workspace_size(const gdn_shape* shape, const int32
   if (!bytes) return gdn::fail(GDN_ERR_NULL_ARG, "bytes is NULL");
   gdn::Plan pt, ps;
   size_t off_s = 0;
-  return gdn::fused_plans(shape, cu_tail_host, cu_suf_host, &pt, &ps, &off_s, bytes);
+  return gdn::fused_plans(shape, cu_tail_host, cu_suf_host, SIZE_MAX, &pt, &ps, &off_s, bytes);
 }
 
 gdn_status gdn_replay_forward(const gdn_shape* shape, const int32_t* cu_tail_host, const int32_t* cu_tail,

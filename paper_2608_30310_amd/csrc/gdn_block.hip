@@ -128,6 +128,7 @@ gdn_status block_impl(const gdn_la_shape* shape, const gdn_la_weights* w, const 
       (outputs && (misaligned(w->w_out, 16) || misaligned(w->norm_w, 16) || misaligned(out, 16))))
     return bfail(GDN_ERR_UNSUPPORTED, "x, w_in, conv_w, norm_w, w_out and out must be 16-byte aligned");
   if (!workspace) return bfail(GDN_ERR_WORKSPACE, "workspace is NULL");
+  fit_split(workspace_bytes, &p);
   if (workspace_bytes < p.bytes)
     return bfail(GDN_ERR_WORKSPACE, "workspace too small: need " + std::to_string(p.bytes) + " bytes, got " +
                                         std::to_string(workspace_bytes));

@@ -161,12 +161,21 @@ struct BlockPlan {
 gdn_status make_block_plan(const gdn_la_shape* shape, const int32_t* cu_seqlens_host,
                            bool with_outputs, BlockPlan* plan, std::string* err);
 
-// Takes the split back: the same plan as one chain, without the halves' states
-// (which come last in the workspace).
-inline void drop_split(Plan* p) {
-  if (!p->split) return;
+// A workspace of `have` bytes that holds the chunk records of fp32 tails but not
+// the halves' states (which come last in it) runs them as one chain, so that a
+// workspace sized for one chain stays enough; bf16 tails need the plan's bytes.
+inline void fit_split(const gdn_shape& s, size_t have, Plan* p) {
+  if (!p->split || s.qkv_dtype != GDN_F32 || have >= p->bytes) return;
   p->split = false;
   p->bytes = p->off_M2;
+}
+// The same for the layer: its recurrence's workspace lies before the GEMM's.
+inline void fit_split(size_t have, BlockPlan* p) {
+  if (have >= p->bytes) return;
+  const size_t whole = p->scan_plan.bytes;
+  fit_split(p->scan, 0, &p->scan_plan);
+  p->off_gemm -= whole - p->scan_plan.bytes;
+  p->bytes -= whole - p->scan_plan.bytes;
 }
 
 // The thread-local message behind gdn_last_error(), shared by every entry point.

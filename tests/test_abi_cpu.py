@@ -163,6 +163,49 @@ def test_tail_replay_rejects_before_launch(case):
     assert st == want, lib.gdn_last_error().decode()
 
 
+# 24 chunks at 16/32 heads of 128 run in two halves where the workspace holds
+# their states, 4 MiB behind the chunk records
+HALVES = 32 * 128 * (128 + 128) * 4
+
+
+@needs_no_gpu
+@pytest.mark.parametrize("short,status", [(0, 1), (1, 1), (HALVES, 1), (HALVES + 1, 5)])
+def test_fp32_tails_need_no_more_than_one_chain(short, status):
+    # a workspace that holds one chain's records is enough for fp32 inputs (a
+    # NULL state_out, which is looked at next, shows that it was accepted)
+    lib = gdn.load_library()
+    shape, cu = _shape(qkv_dtype=binding.GDN_F32), _cu([0, 1536])
+    st, need = _ws_size(shape, cu)
+    assert st == 0 and need == 27197440
+    st = lib.gdn_tail_replay(ctypes.byref(shape), ctypes.cast(cu, ctypes.c_void_p), FAKE, FAKE, FAKE, FAKE, FAKE,
+                             None, ctypes.c_void_p(0x10000), need - short, None)
+    assert st == status, lib.gdn_last_error().decode()
+    # the fused call: the tail's part as above, the suffix's records behind it
+    cs = _cu([0, 100])
+    out = ctypes.c_size_t(0)
+    assert lib.gdn_replay_forward_workspace_size(ctypes.byref(shape), ctypes.cast(cu, ctypes.c_void_p),
+                                                 ctypes.cast(cs, ctypes.c_void_p), ctypes.byref(out)) == 0
+    st = lib.gdn_replay_forward(ctypes.byref(shape), ctypes.cast(cu, ctypes.c_void_p), FAKE, FAKE, FAKE, FAKE, FAKE,
+                                ctypes.cast(cs, ctypes.c_void_p), FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, None, FAKE,
+                                None, ctypes.c_void_p(0x10000), out.value - short, None)
+    assert st == status, lib.gdn_last_error().decode()
+
+
+@needs_no_gpu
+def test_a_workspace_for_two_shorter_fp32_tails_holds_one_tail():
+    lib = gdn.load_library()
+    shape = _shape(qkv_dtype=binding.GDN_F32)
+    _, have = _ws_size(_shape(num_seqs=2, qkv_dtype=binding.GDN_F32), _cu([0, 768, 1536]))
+    assert have == 23961600
+    args = lambda s: (ctypes.byref(s), ctypes.cast(_cu([0, 1536]), ctypes.c_void_p), FAKE, FAKE, FAKE, FAKE, FAKE,
+                      None, ctypes.c_void_p(0x10000))
+    assert lib.gdn_tail_replay(*args(shape), have, None) == 1
+    # bf16 tails in two halves need the size that gdn_workspace_size states
+    _, need = _ws_size(_shape(), _cu([0, 1536]))
+    assert lib.gdn_tail_replay(*args(_shape()), need, None) == 1
+    assert lib.gdn_tail_replay(*args(_shape()), need - 1, None) == 5
+
+
 @needs_no_gpu
 @pytest.mark.parametrize("case", ["null_q", "null_o", "overlap", "small_ws", "misaligned_o"])
 def test_chunk_forward_rejects_before_launch(case):

@@ -119,6 +119,22 @@ def test_block_rejects_before_launch(case):
     assert st == CASES[case], lib.gdn_last_error().decode()
 
 
+@needs_no_gpu
+@pytest.mark.parametrize("short,enough", [(0, True), (32 * 128 * (128 + 128) * 4, True),
+                                          (32 * 128 * (128 + 128) * 4 + 1, False)])
+def test_fp32_state_only_layer_needs_no_more_than_one_chain(short, enough):
+    # as for gdn_tail_replay; a misaligned workspace, which is looked at next,
+    # shows that its size was accepted
+    lib = gdn.load_library()
+    shape, cu = _shape(act_dtype=binding.GDN_F32), _cu([0, 1536])
+    st, need = _ws(shape, cu, False)
+    assert st == 0
+    w = binding.LAWeights(FAKE.value, FAKE.value, FAKE.value, FAKE.value, FAKE.value, FAKE.value)
+    st = lib.gdn_la_block_replay(ctypes.byref(shape), ctypes.byref(w), ctypes.cast(cu, ctypes.c_void_p), FAKE, FAKE,
+                                 FAKE, None, ctypes.c_void_p(0x10010), need - short, None)
+    assert st == 5 and (b"aligned" in lib.gdn_last_error()) == enough, lib.gdn_last_error().decode()
+
+
 def test_block_with_no_sequences_does_nothing():
     # N = 0: every stage has nothing to do, so nothing touches a device
     lib = gdn.load_library()

@@ -308,6 +308,35 @@ def test_fp32_tail_in_two_halves_and_in_64_columns(dk, dv):
                                                         xi["cu_host"])), f"sequence {i}"
 
 
+def test_fp32_tail_in_a_workspace_for_one_chain():
+    # 24 chunks of slowly decaying fp32 tokens in a workspace without room for
+    # the halves' states run as one chain: the bits of the same sequence in a
+    # batch whose split grid does not fit on the chip, in tail_replay, in the
+    # fused call and (there against the two halves, within the split operands'
+    # error) in the state-only layer.
+    import dataclasses
+    shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="f32")
+    t = synth.tokens(211, 0, 0, 0, 1536, shape, gate_scale=0.002)
+    t = dataclasses.replace(t, beta=(t.beta * 0.1).astype(np.float32))
+    x, x2 = device_inputs(synth.pack([t])), device_inputs(synth.pack([t, t]))
+    halves = 32 * 128 * (128 + 128) * 4
+    ws = torch.empty(gdn.workspace_size(1, 16, 32, 128, 128, [0, 1536], dtype=torch.float32) - halves,
+                     dtype=torch.uint8, device="cuda")
+    chain = gdn.tail_replay(x2["k"], x2["v"], x2["g"], x2["beta"], x2["cu"], x2["cu_host"])[:1]
+    split = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    got = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"], workspace=ws)
+    assert torch.equal(got, chain)
+    assert state_err(to_f64(got), to_f64(split)) <= 2e-5
+    y = device_inputs(synth.pack([_seq(1, 100, shape=shape)]))
+    need = gdn.replay_forward_workspace_size(1, 16, 32, 128, 128, [0, 1536], [0, 100], dtype=torch.float32)
+    ws = torch.empty(need - halves, dtype=torch.uint8, device="cuda")
+    o, mid, fin = gdn.replay_forward(x["k"], x["v"], x["g"], x["beta"], x["cu"], y["q"], y["k"], y["v"], y["g"],
+                                     y["beta"], y["cu"], cu_tail_host=x["cu_host"], cu_suf_host=y["cu_host"],
+                                     workspace=ws)
+    o2, fin2 = gdn.chunk_forward(y["q"], y["k"], y["v"], y["g"], y["beta"], y["cu"], y["cu_host"], state_in=chain)
+    assert torch.equal(mid, chain) and torch.equal(fin, fin2) and torch.equal(o, o2)
+
+
 def test_fp32_forward_beyond_the_chip_bitwise():
     # fp32 inputs with outputs: 72 varlen sequences x 4 heads need 1152
     # 32-column workgroups, more than the chip holds, and run in that form over
