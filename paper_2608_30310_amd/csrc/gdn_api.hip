@@ -35,7 +35,7 @@ namespace {
 constexpr int kThreads = 256;
 // grid limits in make_plan assume <= 1024 work items per (sequence, head) in any
 // grid dimension; the column-split scan's grid is bounded by the CU count instead
-static_assert(kThreads <= 256 && kDecodeThreads <= 1024 && head_threads(128) <= 1024, "grid limits");
+static_assert(kThreads <= 256 && kDecodeThreads <= 1024 && kHeadThreads <= 1024, "grid limits");
 
 // ------------------------------------------------------------ host side
 gdn_status fail(gdn_status st, const std::string& msg) {
@@ -53,6 +53,7 @@ gdn_status check_launch(const char* what) {
 struct Args {
   const gdn_shape* s;
   const Plan* p;
+  const int32_t* cu_host;
   const int32_t* cu;
   const void* q;
   const void* k;
@@ -138,9 +139,9 @@ gdn_status cols_fit(const gdn_shape& s, bool* fits, uint32_t* col_groups, int* c
 // `marks` (tail replay only, may be NULL): the call whose stage events are
 // recorded; its combine stage starts before k_state_combine.
 template <typename TIn, int DK, int DV, bool FWD>
-gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, const void* v, const void* k,
-                       const void* q, const float* state_in, void* o, float* state_out, char* ws, hipStream_t stream,
-                       const Args* marks = nullptr, bool* combined = nullptr) {
+gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu_host, const int32_t* cu, const void* v,
+                       const void* k, const void* q, const float* state_in, void* o, float* state_out, char* ws,
+                       hipStream_t stream, const Args* marks = nullptr, bool* combined = nullptr) {
   const u32x4* Kw = reinterpret_cast<const u32x4*>(ws + p.off_K);
   const u32x4* Tw = reinterpret_cast<const u32x4*>(ws + p.off_T);
   const float* Sw = reinterpret_cast<const float*>(ws + p.off_S);
@@ -196,12 +197,21 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
                        static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw, Pw, state_in,
                        static_cast<TIn*>(o), state_out);
   } else if constexpr (!FWD) {
-    // One 16-column tile per wave, 64 columns per workgroup: fp32 batches, those
-    // whose grid fits on the chip so (3 sequences of 32 heads: 178 -> 88 us
-    // against the wide scan), and those for which the plan prefers it (see
-    // Plan::wide_tail).
+    // A batch that fits on the chip with 64 columns per workgroup runs so (3
+    // sequences of 32 heads: 178 -> 88 us against the wide scan), others as the
+    // plan prefers (see TailScan).
     const int64_t groups64 = static_cast<int64_t>(s.num_seqs) * s.num_v_heads * (s.d_v / kSplitCols2);
-    if (sizeof(TIn) == 4 || groups64 <= cus || !p.wide_tail) {
+    const TailScan tail = groups64 <= cus ? TailScan::kRounds : tail_scan(s, cu_host, p);
+    if constexpr (sizeof(TIn) == 4 && DV == 128) {
+      if (tail == TailScan::kHead) {
+        hipLaunchKernelGGL((k_scan_head<TIn, DK, FWD>), dim3(static_cast<uint32_t>(s.num_seqs) * s.num_v_heads),
+                           dim3(kHeadThreads), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
+                           static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw,
+                           Sw, Pw, state_in, static_cast<TIn*>(o), state_out);
+        return check_launch("scan launch");
+      }
+    }
+    if (tail != TailScan::kWide) {
       hipLaunchKernelGGL((k_scan_cols_64<TIn, DK>), dim3(static_cast<uint32_t>(groups64)),
                          dim3((kSplitCols2 / 16 + 1) * kWave), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
                          s.d_v, static_cast<const TIn*>(v), static_cast<const TIn*>(k), Kw, Tw, Sw, state_out);
@@ -268,8 +278,8 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu, con
         if (peel >= s.num_seqs || static_cast<int64_t>(peel) * s.num_v_heads * per_head > cus) peel = 0;
       }
       const int32_t n_head = s.num_seqs - peel;
-      hipLaunchKernelGGL((k_scan_head<TIn, DK, DV, FWD>), dim3(static_cast<uint32_t>(n_head) * s.num_v_heads),
-                         dim3(head_threads(DV)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
+      hipLaunchKernelGGL((k_scan_head<TIn, DK, FWD>), dim3(static_cast<uint32_t>(n_head) * s.num_v_heads),
+                         dim3(kHeadThreads), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads,
                          static_cast<const TIn*>(v), static_cast<const TIn*>(k), static_cast<const TIn*>(q), Kw, Tw, Sw,
                          Pw, state_in, static_cast<TIn*>(o), state_out);
       if (peel > 0) {
@@ -293,9 +303,8 @@ gdn_status run(const Args& a) {
     return st;
   if ((st = mark(a, 1)) != GDN_OK) return st;
   bool combined = false;
-  if ((st = launch_scan<TIn, DK, DV, FWD>(s, *a.p, a.cu, a.v, a.k, a.q, a.state_in, a.o, a.state_out, a.ws,
-                                          a.stream,
-                                          FWD ? nullptr : &a, &combined)) != GDN_OK)
+  if ((st = launch_scan<TIn, DK, DV, FWD>(s, *a.p, a.cu_host, a.cu, a.v, a.k, a.q, a.state_in, a.o, a.state_out,
+                                          a.ws, a.stream, FWD ? nullptr : &a, &combined)) != GDN_OK)
     return st;
   if (!FWD && !combined) {
     // one chain: the combine stage is empty
@@ -376,7 +385,7 @@ gdn_status tail_replay_impl(const gdn_shape* shape, const int32_t* cu_seqlens_ho
     return gdn::fail(GDN_ERR_NULL_ARG, "k, v, g and beta must be non-NULL");
   if (reinterpret_cast<uintptr_t>(k) % 16 != 0 || reinterpret_cast<uintptr_t>(v) % 16 != 0)
     return gdn::fail(GDN_ERR_UNSUPPORTED, "k and v must be 16-byte aligned");
-  const gdn::Args a{shape, &plan, cu_seqlens, nullptr, k, v, g, beta, nullptr,
+  const gdn::Args a{shape, &plan, cu_seqlens_host, cu_seqlens, nullptr, k, v, g, beta, nullptr,
                     nullptr, state_out, static_cast<char*>(workspace),
                     static_cast<hipStream_t>(stream), events};
   if (shape->num_seqs == 0) return mark_all(a, false);
@@ -408,7 +417,7 @@ gdn_status chunk_forward_impl(const gdn_shape* shape, const int32_t* cu_seqlens_
     if (a0 < b1 && b0 < a1)
       return gdn::fail(GDN_ERR_BAD_SHAPE, "state_out overlaps state_in without being equal");
   }
-  const gdn::Args a{shape, &plan, cu_seqlens, q, k, v, g, beta, state_in,
+  const gdn::Args a{shape, &plan, cu_seqlens_host, cu_seqlens, q, k, v, g, beta, state_in,
                     o, state_out, static_cast<char*>(workspace),
                     static_cast<hipStream_t>(stream), events};
   if (shape->num_seqs == 0) return mark_all(a, true);
@@ -427,6 +436,7 @@ struct FusedArgs {
   const gdn_shape* s;
   const Plan* pt;      // tail plan (no outputs)
   const Plan* ps;      // suffix plan (outputs)
+  const int32_t* cu_t_host;
   const int32_t* cu_t;
   const void* k_t;
   const void* v_t;
@@ -510,17 +520,16 @@ gdn_status run_fused(const FusedArgs& a) {
                        reinterpret_cast<float*>(a.ws_s + ps.off_S), reinterpret_cast<u32x4*>(a.ws_s + ps.off_P));
     if ((st = check_launch("tail scan + suffix intra launch")) != GDN_OK) return st;
   } else if (!combine) {
-    if ((st = launch_scan<TIn, DK, DV, false>(s, pt, a.cu_t, a.v_t, a.k_t, nullptr, nullptr, nullptr, a.state_mid,
-                                              a.ws_t,
-                                              a.stream)) != GDN_OK)
+    if ((st = launch_scan<TIn, DK, DV, false>(s, pt, a.cu_t_host, a.cu_t, a.v_t, a.k_t, nullptr, nullptr, nullptr,
+                                              a.state_mid, a.ws_t, a.stream)) != GDN_OK)
       return st;
     if ((st = launch_intra<TIn, DK, true>(s, ps, a.cu_s, a.q, a.k, a.g, a.beta, a.ws_s, a.stream)) != GDN_OK)
       return st;
   }
   if (!combine && (st = fmark(a, 2)) != GDN_OK) return st;
   if ((st = fmark(a, 3)) != GDN_OK) return st;
-  if ((st = launch_scan<TIn, DK, DV, true>(s, ps, a.cu_s, a.v, a.k, a.q, a.state_mid, a.o, a.state_out, a.ws_s,
-                                           a.stream)) != GDN_OK)
+  if ((st = launch_scan<TIn, DK, DV, true>(s, ps, nullptr, a.cu_s, a.v, a.k, a.q, a.state_mid, a.o, a.state_out,
+                                           a.ws_s, a.stream)) != GDN_OK)
     return st;
   return fmark(a, 4);
 }
@@ -573,8 +582,8 @@ gdn_status replay_forward_impl(const gdn_shape* shape, const int32_t* cu_tail_ho
     if (state_mid < state_out + n && state_out < state_mid + n)
       return fail(GDN_ERR_BAD_SHAPE, "state_out overlaps state_mid without being equal");
   }
-  const FusedArgs a{shape, &pt, &ps, cu_tail, k_tail, v_tail, g_tail, beta_tail, cu_suf, q, k, v, g, beta,
-                    state_mid, o, state_out, static_cast<char*>(workspace),
+  const FusedArgs a{shape, &pt, &ps, cu_tail_host, cu_tail, k_tail, v_tail, g_tail, beta_tail, cu_suf, q, k, v, g,
+                    beta, state_mid, o, state_out, static_cast<char*>(workspace),
                     static_cast<char*>(workspace) + off_s, static_cast<hipStream_t>(stream), events};
   if (shape->num_seqs == 0) {
     for (int i = 0; i <= kNumFusedStages; ++i)

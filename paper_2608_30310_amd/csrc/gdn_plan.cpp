@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <functional>
 #include <limits>
 
 namespace gdn {
@@ -22,6 +23,73 @@ thread_local std::string t_last_error;
 
 void set_last_error(const std::string& msg) { t_last_error = msg; }
 const char* last_error() { return t_last_error.c_str(); }
+
+namespace {
+
+// Chunk count of the sequence of rank r, longest first; 0 past the last.
+struct Ranked {
+  const int32_t* cu;
+  const SeqOrder* order;
+  int64_t n;
+  int64_t operator()(int64_t r) const {
+    if (r >= n) return 0;
+    const int64_t i = order->n > 0 ? order->seq[r] : r;
+    return (static_cast<int64_t>(cu[i + 1]) - cu[i] + kChunk - 1) / kChunk;
+  }
+};
+
+// When the last of the chains ends if `lanes` of them run at once and the next
+// starts as one ends; one of c chunks takes start + per_chunk c.
+double last_end(const Ranked& chunks, int64_t lanes, double per_chunk, double start) {
+  const auto time = [&](int64_t r) { return start + per_chunk * static_cast<double>(chunks(r)); };
+  const int64_t n = std::min(lanes, chunks.n);
+  double end = time(0);
+  if (n == chunks.n) return end;   // all at once
+  double busy[kMaxOrderedSeqs];    // a heap, the lane that is free first in front
+  for (int64_t r = 0; r < n; ++r) busy[n - 1 - r] = time(r);
+  for (int64_t r = n; r < chunks.n; ++r) {
+    std::pop_heap(busy, busy + n, std::greater<double>());
+    end = std::max(end, busy[n - 1] += time(r));
+    std::push_heap(busy, busy + n, std::greater<double>());
+  }
+  return end;
+}
+
+// The same without an order (more than kMaxOrderedSeqs) or where one sequence's
+// heads are more than fit: the work per place plus the longest chain, of which
+// a quarter overlaps where there are many sequences.
+double last_end_estimate(const Plan& p, int64_t n, double lanes, double per_chunk, double start) {
+  const double work = start * static_cast<double>(n) + per_chunk * static_cast<double>(p.num_chunks);
+  return work / lanes + (n > kMaxOrderedSeqs ? 0.75 : 1.0) * (start + per_chunk * p.max_chunks);
+}
+
+}  // namespace
+
+TailScan tail_scan(const gdn_shape& s, const int32_t* cu, const Plan& p) {
+  const int64_t N = s.num_seqs, hv = s.num_v_heads;
+  const int64_t groups = hv * (s.d_v / 64);   // 64-column workgroups of a sequence
+  if (N * groups <= kSplitMaxGroups) return TailScan::kRounds;
+  const Ranked ranked{cu, &p.order, N};
+  if (s.qkv_dtype == GDN_F32) {
+    if (s.d_v != 128) return TailScan::kRounds;
+    constexpr double kRoundStart = 1.8, kHeadChunk = 2.2, kHeadStart = 1.5;
+    const bool ordered = N <= kMaxOrderedSeqs && groups <= kSplitMaxGroups;
+    const double per64 = static_cast<double>(kSplitMaxGroups) / static_cast<double>(groups);
+    const double rounds = ordered ? last_end(ranked, kSplitMaxGroups / groups, 1.0, kRoundStart)
+                                  : last_end_estimate(p, N, per64, 1.0, kRoundStart);
+    const double head = ordered ? last_end(ranked, kSplitMaxGroups / hv, kHeadChunk, kHeadStart)
+                                : last_end_estimate(p, N, 2 * per64, kHeadChunk, kHeadStart);
+    return rounds > head ? TailScan::kHead : TailScan::kRounds;
+  }
+  if (N > kMaxOrderedSeqs) return TailScan::kWide;
+  const int64_t per_round = kSplitMaxGroups / groups;
+  const int64_t resident = 2 * kSplitMaxGroups / hv / (s.d_v == 64 ? 1 : 2);
+  if (per_round == 0) return TailScan::kWide;
+  int64_t steps = 0;
+  for (int64_t r = 0; r < N; r += per_round) steps += ranked(r);
+  const bool wide = steps > 1.7 * static_cast<double>(ranked(0)) + static_cast<double>(ranked(resident));
+  return wide ? TailScan::kWide : TailScan::kRounds;
+}
 
 gdn_status check_shape(const gdn_shape* shape, std::string* err) {
   if (!shape) { *err = "shape is NULL"; return GDN_ERR_NULL_ARG; }
@@ -109,21 +177,6 @@ gdn_status make_plan(const gdn_shape* shape, const int32_t* cu, bool with_output
     std::stable_sort(idx, idx + N, [&](int32_t a, int32_t b) { return nch(a) > nch(b); });
     p.order.n = N;
     for (int32_t n = 0; n < N; ++n) p.order.seq[n] = idx[n];
-  }
-  if (!with_outputs && N <= kMaxOrderedSeqs) {
-    // chunk count of the sequence of rank r, longest first
-    auto ranked = [&](int64_t r) -> int64_t {
-      if (r >= N) return 0;
-      const int32_t n = p.order.n > 0 ? p.order.seq[r] : static_cast<int32_t>(r);
-      return (static_cast<int64_t>(cu[n + 1]) - cu[n] + kChunk - 1) / kChunk;
-    };
-    const int64_t per_round = kSplitMaxGroups / (static_cast<int64_t>(hv) * (shape->d_v / 64));
-    const int64_t resident = 2 * kSplitMaxGroups / hv / (shape->d_v == 64 ? 1 : 2);
-    if (per_round > 0) {
-      int64_t steps = 0;
-      for (int64_t r = 0; r < N; r += per_round) steps += ranked(r);
-      p.wide_tail = steps > 1.7 * static_cast<double>(ranked(0)) + static_cast<double>(ranked(resident));
-    }
   }
   p.split = !with_outputs && max_chunks >= split_min_chunks(shape->qkv_dtype == GDN_F32) &&
             split_groups(*shape) <= kSplitMaxGroups;

@@ -63,6 +63,27 @@ struct SeqOrder {
   int32_t seq[kMaxOrderedSeqs];
 };
 
+// Tail replay of a batch whose 64-column grid does not fit on the chip at once.
+//   kRounds  one 16-column tile per wave in 64-column workgroups, one per CU, in
+//            rounds, longest first: the shortest chunks (~1.55 us for bf16
+//            inputs, ~2 for fp32 at d_k = 128), the unit of the estimates
+//   kWide    bf16 inputs: two tiles per wave, all of whose workgroups are
+//            resident from the start, two per CU.  ~1.7 x the longest chain
+//            (alone on its CU, ~2.9 us a chunk) plus the longest chain that
+//            shares a CU.  Measured at 32 heads, d = 128: 5, 8 and 12 chains of
+//            32 chunks 101, 108 and 157 us in rounds, 93, 99 and 148 wide; 6
+//            and 8 ragged ones (52 against 91 and 83 against 102 steps) 73 and
+//            120 against 115 and 135; 12 and 16 ragged ones 150 and 186 against
+//            137 and 169.
+//   kHead    fp32 inputs, d_v = 128: a head per workgroup (eight waves), half as
+//            many workgroups.  A chunk takes 2.2 units, but each workgroup also
+//            costs ~1.5 units to start (a 64-column one 1.8), so it wins where
+//            chains are short and where two rounds are full: 16 sequences x 32
+//            heads of 1, 2 and 4 chunks 33.6, 45.7 and 67.1 us against 38.2, 48.9
+//            and 69.5 in rounds, 36 of which one has 7 chunks and the others one
+//            60.4 against 71.5; but 12 of 7 chunks 94.9 against 86.3.
+enum class TailScan { kRounds, kWide, kHead };
+
 // Where each region lives inside the caller's workspace, and the launch sizes.
 struct Plan {
   int64_t total_tokens = 0;
@@ -79,17 +100,6 @@ struct Plan {
   // Longest-first order of the sequences, for scans whose grid exceeds the
   // chip (passed by value in the kernel's arguments)
   SeqOrder order;
-  // Tail replay of bf16 batches beyond the chip: two tiles per wave (the wide
-  // scan, all of whose workgroups are resident from the start) rather than one
-  // tile per wave in rounds of 64-column workgroups.  In units of the latter's
-  // chunk time (~1.55 us) the rounds take the sum of each round's longest
-  // chain, the wide scan ~1.7 x the longest chain (alone on its CU, ~2.9 us a
-  // chunk) plus the longest chain that shares a CU.  Measured at 32 heads, d =
-  // 128: 5, 8 and 12 chains of 32 chunks 101, 108 and 157 us in rounds, 93, 99
-  // and 151 wide; 6 and 8 ragged ones (52 against 91 and 83 against 102 steps)
-  // 73 and 120 against 115 and 135; 12 and 16 ragged ones 150 and 186 against
-  // 137 and 169.
-  bool wide_tail = true;
   // Tail replay in two halves (see split_groups): the second half's state
   // from zero and its transition, fp32
   bool split = false;
@@ -97,6 +107,10 @@ struct Plan {
   size_t off_A2 = 0;              // [N, Hv, d_k, d_k]
   size_t bytes = 0;               // total workspace size
 };
+
+// The form for a batch of these tails; `p` is their plan without outputs.  A call
+// asks once, when it launches (~1 us on the host for 256 unequal sequences).
+TailScan tail_scan(const gdn_shape& s, const int32_t* cu_seqlens_host, const Plan& p);
 
 // Tail replay may run as two half-length scans and a combine
 // when every workgroup of the split grid fits on the chip at once (one per CU):

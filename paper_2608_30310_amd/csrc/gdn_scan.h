@@ -1563,19 +1563,23 @@ void k_scan_cols_intra(int32_t n_scan, const int32_t* __restrict__ cu_t, int32_t
 }
 
 // ---------------------------------------------------------------- throughput kernel
-// grid = N x Hv: d_v/16 waves (two per SIMD for d_v = 128), each 16 columns,
-// sharing one copy of the chunk's records per head; every wave issues an equal
-// share of the next chunk's DMA, spread over the chunk's regions.  Used when
-// the latency kernel's grid would not fit on the chip at once.
-constexpr int head_threads(int dv) { return dv / 16 * kWave; }
+// d_v = 128, grid = N x Hv: eight waves (two per SIMD), each 16 columns, sharing
+// one copy of the chunk's records per head; every wave issues an equal share of
+// the next chunk's DMA, spread over the chunk's regions (fp32 inputs at d_k = 128
+// hold one chunk in LDS and issue it between two).  Used for bf16 batches with
+// outputs and fp32 tail replay batches beyond the chip (see launch_scan and
+// TailScan).
+constexpr int kHeadCols = 128;
+constexpr int kHeadThreads = kHeadCols / 16 * kWave;
 
-template <typename TIn, int DK, int DV, bool FWD>
-__global__ __launch_bounds__(head_threads(DV))
+template <typename TIn, int DK, bool FWD>
+__global__ __launch_bounds__(kHeadThreads)
 void k_scan_head(const int32_t* __restrict__ cu, const SeqOrder order, int32_t hk, int32_t hv,
                  const TIn* __restrict__ v, const TIn* __restrict__ kin, const TIn* __restrict__ qin,
                  const u32x4* __restrict__ Kw, const u32x4* __restrict__ Tw,
                  const float* __restrict__ Sw, const u32x4* __restrict__ Pw,
                  const float* __restrict__ state_in, TIn* __restrict__ o, float* __restrict__ state_out) {
+  constexpr int DV = kHeadCols;
   using L = ScanLds<TIn, DK, DV, FWD, true>;
   constexpr int NT = DK / 16;
   constexpr int W = DV / 16;

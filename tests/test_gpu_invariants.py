@@ -308,6 +308,23 @@ def test_fp32_tail_in_two_halves_and_in_64_columns(dk, dv):
                                                         xi["cu_host"])), f"sequence {i}"
 
 
+@pytest.mark.parametrize("dk", [64, 128])
+@pytest.mark.parametrize("lens", [[128] * 5, [63, 64, 65, 127, 128], [420] + [1 + 7 * i % 64 for i in range(35)],
+                                  [0, 700, 1] + [300] * 6], ids=["two_chunks", "edges", "one_longer", "rounds"])
+def test_fp32_tail_batches_beyond_the_chip_bitwise(lens, dk):
+    # fp32 batches of 32 heads with d_v = 128: short chains and full rounds run
+    # a head per workgroup, others 64 columns.  Same products, same order as
+    # each sequence's own call (one chain, 32 columns per workgroup).
+    shape = synth.Shape(hk=16, hv=32, dk=dk, dv=128, dtype="f32")
+    seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
+    x = device_inputs(synth.pack(seqs))
+    st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    for i, n in enumerate(lens):
+        xi = device_inputs(synth.pack([seqs[i]]))
+        sti = gdn.tail_replay(xi["k"], xi["v"], xi["g"], xi["beta"], xi["cu"], xi["cu_host"])
+        assert torch.equal(st[i:i + 1], sti), f"sequence {i} (length {n})"
+
+
 def test_fp32_tail_in_a_workspace_for_one_chain():
     # 24 chunks of slowly decaying fp32 tokens in a workspace without room for
     # the halves' states run as one chain: the bits of the same sequence in a
