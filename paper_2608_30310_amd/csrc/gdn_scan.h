@@ -1106,8 +1106,8 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
     wait_dma();
   }
   __syncthreads();
-  each_chunk<L::kBuffers>(nch, [&](int j, auto bc) __attribute__((always_inline)) {
-    constexpr int b = decltype(bc)::value;
+  auto chunk = [&](int j, auto bc) __attribute__((always_inline)) {
+    const int b = bc;
     const unsigned char* buf = (const unsigned char*)(lds_l + b * L::kBytes);
     if constexpr (NC > 1) {
       // without a DMA wave: the next chunk's share, spread over the phases
@@ -1123,7 +1123,17 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
       chunk_step<L, DK, false, false>(buf, 16 * wave, lane, M[0], mb[0], none, [](int) {});
     }
     __syncthreads();     // next chunk's operands are in LDS (every wave's share)
-  });
+  };
+  // The buffers in turn with constant LDS addresses, but for bf16 chains of d_k =
+  // 64 in 64 columns: their short chunk gains less from them than the doubled
+  // loop costs (one of 52 chunks among 6 sequences of 32 heads: 68.9 us so, 65.6
+  // with the buffer as a variable; at d_k = 128 89.2 and 89.5, and the two halves'
+  // split scan is ahead with constants, 42.0 against 42.5).
+  if constexpr (DK == 64 && COLS == kSplitCols2 && NC == 1 && !SPLIT && !L::kSplit) {
+    for (int j = 0; j < nch; ++j) chunk(j, j & 1);
+  } else {
+    each_chunk<L::kBuffers>(nch, chunk);
+  }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     if (SPLIT && ident) {
