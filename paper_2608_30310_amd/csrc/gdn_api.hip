@@ -218,19 +218,12 @@ gdn_status launch_scan(const gdn_shape& s, const Plan& p, const int32_t* cu_host
       return check_launch("scan launch");
     }
     if constexpr (sizeof(TIn) == 2) {
-      // Otherwise a whole head per workgroup (128 columns, four compute waves)
-      // where d_v allows, two workgroups per CU.  When the last round of that
-      // grid would be partly empty and its sequences fit on the chip at one
-      // 64-column workgroup per CU, those sequences (the shortest, in
-      // longest-first order) run in the one-tile scan after it instead.
-      constexpr int kCols = DV >= 128 ? 128 : 64;
-      const int64_t per_seq = static_cast<int64_t>(s.num_v_heads) * (s.d_v / kCols);
-      const int64_t rem = static_cast<int64_t>(s.num_seqs) * per_seq % (2 * static_cast<int64_t>(cus));
-      int32_t peel = 0;
-      if (rem > 0 && s.num_seqs <= kMaxOrderedSeqs) {
-        peel = static_cast<int32_t>((rem + per_seq - 1) / per_seq);
-        if (peel >= s.num_seqs || static_cast<int64_t>(peel) * s.num_v_heads * (s.d_v / kSplitCols2) > cus) peel = 0;
-      }
+      // Otherwise a whole head per workgroup (two 16-column tiles per wave), two
+      // workgroups per CU, then the sequences peeled off its last round in the
+      // one-tile scan.
+      constexpr int kCols = DV;
+      const int64_t per_seq = s.num_v_heads;
+      const int32_t peel = wide_peel(s, cus);
       const int32_t n_wide = s.num_seqs - peel;
       hipLaunchKernelGGL((k_scan_cols_wide<TIn, DK, kCols>), dim3(static_cast<uint32_t>(n_wide * per_seq)),
                          dim3(cols_wide_threads(kCols)), 0, stream, cu, p.order, s.num_k_heads, s.num_v_heads, s.d_v,

@@ -56,39 +56,59 @@ double last_end(const Ranked& chunks, int64_t lanes, double per_chunk, double st
 }
 
 // The same without an order (more than kMaxOrderedSeqs) or where one sequence's
-// heads are more than fit: the work per place plus the longest chain, of which
-// a quarter overlaps where there are many sequences.
-double last_end_estimate(const Plan& p, int64_t n, double lanes, double per_chunk, double start) {
+// heads are more than fit: the work per place plus `longest` of the longest
+// chain.
+double last_end_estimate(const Plan& p, int64_t n, double lanes, double per_chunk, double start, double longest) {
   const double work = start * static_cast<double>(n) + per_chunk * static_cast<double>(p.num_chunks);
-  return work / lanes + (n > kMaxOrderedSeqs ? 0.75 : 1.0) * (start + per_chunk * p.max_chunks);
+  return work / lanes + longest * (start + per_chunk * p.max_chunks);
 }
 
 }  // namespace
+
+int32_t wide_peel(const gdn_shape& s, int64_t cus) {
+  const int64_t rem = static_cast<int64_t>(s.num_seqs) * s.num_v_heads % (2 * cus);
+  if (rem == 0 || s.num_seqs > kMaxOrderedSeqs) return 0;
+  const int64_t peel = (rem + s.num_v_heads - 1) / s.num_v_heads;
+  return peel >= s.num_seqs || peel * s.num_v_heads * (s.d_v / 64) > cus ? 0 : static_cast<int32_t>(peel);
+}
 
 TailScan tail_scan(const gdn_shape& s, const int32_t* cu, const Plan& p) {
   const int64_t N = s.num_seqs, hv = s.num_v_heads;
   const int64_t groups = hv * (s.d_v / 64);   // 64-column workgroups of a sequence
   if (N * groups <= kSplitMaxGroups) return TailScan::kRounds;
   const Ranked ranked{cu, &p.order, N};
+  const double per64 = static_cast<double>(kSplitMaxGroups) / static_cast<double>(groups);   // sequences a round
   if (s.qkv_dtype == GDN_F32) {
     if (s.d_v != 128) return TailScan::kRounds;
     constexpr double kRoundStart = 1.8, kHeadChunk = 2.2, kHeadStart = 1.5;
     const bool ordered = N <= kMaxOrderedSeqs && groups <= kSplitMaxGroups;
-    const double per64 = static_cast<double>(kSplitMaxGroups) / static_cast<double>(groups);
+    const double longest = N > kMaxOrderedSeqs ? 0.75 : 1.0;
     const double rounds = ordered ? last_end(ranked, kSplitMaxGroups / groups, 1.0, kRoundStart)
-                                  : last_end_estimate(p, N, per64, 1.0, kRoundStart);
+                                  : last_end_estimate(p, N, per64, 1.0, kRoundStart, longest);
     const double head = ordered ? last_end(ranked, kSplitMaxGroups / hv, kHeadChunk, kHeadStart)
-                                : last_end_estimate(p, N, 2 * per64, kHeadChunk, kHeadStart);
+                                : last_end_estimate(p, N, 2 * per64, kHeadChunk, kHeadStart, longest);
     return rounds > head ? TailScan::kHead : TailScan::kRounds;
   }
-  if (N > kMaxOrderedSeqs) return TailScan::kWide;
-  const int64_t per_round = kSplitMaxGroups / groups;
-  const int64_t resident = 2 * kSplitMaxGroups / hv / (s.d_v == 64 ? 1 : 2);
-  if (per_round == 0) return TailScan::kWide;
-  int64_t steps = 0;
-  for (int64_t r = 0; r < N; r += per_round) steps += ranked(r);
-  const bool wide = steps > 1.7 * static_cast<double>(ranked(0)) + static_cast<double>(ranked(resident));
-  return wide ? TailScan::kWide : TailScan::kRounds;
+  // the wide scan's cost in chunks of the rounds (see TailScan)
+  struct Wide { double alone, shared, peeled, start, unordered; };
+  const Wide w = s.d_v == 128   ? Wide{1.7, 0.7, 0, 0.9, 2.46}
+                 : s.d_k == 128 ? Wide{1.65, 0.15, 1.1, 0.5, 1.8}
+                                : Wide{1.5, 0.7, 1.5, 0.3, 2.46};
+  const bool big = groups > kSplitMaxGroups;   // one sequence's heads are more than a round
+  if (big && s.d_v == 128) return TailScan::kWide;
+  if (N > kMaxOrderedSeqs || big) {
+    const double rounds = std::min(std::ceil(static_cast<double>(N) / per64) * (w.start + p.max_chunks),
+                                   last_end_estimate(p, N, per64, 1.0, w.start, 1.0));
+    const bool again = big && s.d_k == 128 && N * hv > 2 * kSplitMaxGroups;   // more than are resident
+    return rounds > w.start + (w.unordered + (again ? w.alone : 0)) * p.max_chunks ? TailScan::kWide
+                                                                                   : TailScan::kRounds;
+  }
+  const double rounds = last_end(ranked, kSplitMaxGroups / groups, 1.0, w.start);
+  const int64_t peel = wide_peel(s, kSplitMaxGroups);
+  const double wide = w.start + w.alone * static_cast<double>(ranked(0)) +
+                      w.shared * static_cast<double>(ranked(kSplitMaxGroups / hv)) +
+                      (peel > 0 ? w.peeled * static_cast<double>(ranked(N - peel)) : 0.0);
+  return rounds > wide ? TailScan::kWide : TailScan::kRounds;
 }
 
 gdn_status check_shape(const gdn_shape* shape, std::string* err) {

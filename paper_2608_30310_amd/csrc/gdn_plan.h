@@ -67,14 +67,23 @@ struct SeqOrder {
 //   kRounds  one 16-column tile per wave in 64-column workgroups, one per CU, in
 //            rounds, longest first: the shortest chunks (~1.55 us for bf16
 //            inputs, ~2 for fp32 at d_k = 128), the unit of the estimates
-//   kWide    bf16 inputs: two tiles per wave, all of whose workgroups are
-//            resident from the start, two per CU.  ~1.7 x the longest chain
-//            (alone on its CU, ~2.9 us a chunk) plus the longest chain that
-//            shares a CU.  Measured at 32 heads, d = 128: 5, 8 and 12 chains of
-//            32 chunks 101, 108 and 157 us in rounds, 93, 99 and 148 wide; 6
-//            and 8 ragged ones (52 against 91 and 83 against 102 steps) 73 and
-//            120 against 115 and 135; 12 and 16 ragged ones 150 and 186 against
-//            137 and 169.
+//   kWide    bf16 inputs: two tiles per wave, a head per workgroup, all of them
+//            resident from the start, two per CU.  The longest chain takes 1.7 x
+//            its chunks (alone on its CU, ~2.9 us a chunk) plus 0.7 x those of
+//            the longest one that shares a CU; a workgroup of the rounds costs
+//            0.9 to start.  Measured at 32 heads, d = 128: 5, 8 and 12 sequences
+//            of 13 chunks 60, 65 and 92 us in rounds, 54, 61 and 84 wide; one of
+//            52 among 5, 12 and 24 88, 94 and 99 against 145, 154 and 162.  At
+//            d_v = 64 a workgroup has two waves, and the sequences peeled off the
+//            last round follow the longest chain: at d_k = 128 the second
+//            workgroup on a CU costs little (12 sequences of 13 chunks 70 and 67
+//            us, 24 of them 115 and 114), at d_k = 64 rounds gain more (9, 12, 16
+//            and 24 of 13 chunks 51, 57, 64 and 91 us against 58, 65, 71 and 101).
+//            Beyond 256 sequences, which run in index order, rounds end at best
+//            when each is full, and after the work per place plus the longest
+//            chain; wide ones after 2.46 x the longest (1.8 at d_k = 128, d_v =
+//            64): 300 x 1 head of d = 128 with 13 chunks 86 and 78 us, ragged up
+//            to 26 103 and 120, one of 52 85 and 146.
 //   kHead    fp32 inputs, d_v = 128: a head per workgroup (eight waves), half as
 //            many workgroups.  A chunk takes 2.2 units, but each workgroup also
 //            costs ~1.5 units to start (a 64-column one 1.8), so it wins where
@@ -111,6 +120,11 @@ struct Plan {
 // The form for a batch of these tails; `p` is their plan without outputs.  A call
 // asks once, when it launches (~1 us on the host for 256 unequal sequences).
 TailScan tail_scan(const gdn_shape& s, const int32_t* cu_seqlens_host, const Plan& p);
+
+// Sequences (the shortest) that a wide grid leaves to the 64-column scan after
+// it: those of its partly empty last round, two workgroups on each of `cus` CUs,
+// where they fit at one 64-column workgroup per CU.
+int32_t wide_peel(const gdn_shape& s, int64_t cus);
 
 // Tail replay may run as two half-length scans and a combine
 // when every workgroup of the split grid fits on the chip at once (one per CU):

@@ -77,3 +77,37 @@ def test_fp32_tail_batches_with_one_form(route):
     assert route(16, 32, 128, 64, [1] * 36, binding.GDN_F32) == ROUNDS
     assert route(16, 32, 128, 128, [], binding.GDN_F32) == ROUNDS
     assert route(65535, 65535, 128, 128, [1], binding.GDN_F32) in (ROUNDS, HEAD)
+
+
+# hk, hv, dk, dv, chunks per sequence, us in 64-column rounds, us in the wide scan
+BF16_BATCHES = [
+    (16, 32, 128, 128, [13] * 5, 59.9, 54.2),
+    (16, 32, 128, 128, [52] + [3] * 4, 87.7, 144.5),
+    (16, 32, 128, 128, [2, 4, 2, 4, 2, 4, 2, 4, 2], 31.6, 28.0),
+    (16, 32, 128, 128, [13] * 12, 92.0, 83.9),
+    (16, 32, 128, 128, [52] + [3] * 35, 121.8, 183.5),
+    (1, 140, 128, 128, [13, 7], 81.9, 74.0),
+    (16, 32, 64, 128, [52] + [3] * 4, 62.3, 109.6),
+    (16, 32, 64, 128, [13] * 8, 49.8, 48.6),
+    (16, 32, 128, 64, [13] * 12, 70.4, 67.1),
+    (16, 32, 128, 64, [52] + [3] * 11, 92.8, 147.3),
+    (16, 32, 64, 64, [13] * 9, 51.2, 58.3),
+    (16, 32, 64, 64, [13] * 16, 64.4, 71.1),
+    (16, 32, 64, 64, [13] * 24, 91.4, 101.0),
+    (16, 32, 64, 64, [7] * 17, 51.4, 56.2),
+    (4, 4, 64, 64, [13] * 128, 65.7, 72.1),
+    (2, 300, 64, 64, [7], 37.5, 40.5),
+    # beyond 256 sequences there is no order
+    (1, 1, 128, 128, [13] * 300, 86.1, 78.4),
+    (1, 1, 128, 128, [52] + [3] * 299, 84.9, 145.8),
+    (1, 1, 128, 128, list(range(1, 27)) * 12, 103.4, 120.5),
+    (1, 1, 64, 64, [13] * 300, 54.1, 60.8),
+    (1, 1, 64, 64, [52] + [3] * 599, 70.1, 114.9),
+    (1, 1, 64, 64, [13] * 600, 83.3, 78.8),
+    (4, 4, 64, 64, [52] + [3] * 299, 77.5, 125.0),
+]
+
+
+@pytest.mark.parametrize("hk,hv,dk,dv,chunks,rounds,wide", BF16_BATCHES)
+def test_bf16_tail_batches(route, hk, hv, dk, dv, chunks, rounds, wide):
+    assert route(hk, hv, dk, dv, chunks, binding.GDN_BF16) == (ROUNDS if rounds < wide else WIDE)
