@@ -1195,9 +1195,14 @@ __device__ __forceinline__ void scan_cols_out_body(lds_byte* lds_l, int block, i
   constexpr int NKF = L::kKFrags;
   constexpr int DW = cols_dma_waves(SPLIT, TILES);
   constexpr bool TWO = CL::kBuffers > 1;
-  // output waves that issue DMA store a chunk's outputs after it, in the next
-  // chunk; others at once (32768 tokens: 900 -> 855 us before the third buffer)
-  constexpr bool kDefer = TILES == kOutTiles;
+  // Output waves beside a DMA wave store a chunk's outputs at once (32768 bf16
+  // tokens: 855 us so, 900 in the next chunk, with two buffers).  Those that
+  // issue the DMA wait for it, and for their stores, at the chunk's end: they
+  // store in the next chunk.  Only fp32 chunks of d_k = 128, held one at a time,
+  // are ahead at once (one of 52 chunks 101.9 us against 103.3, 24 sequences of
+  // 6 479 against 484; at d_k = 64 62.9 against 61.6 and 198 against 188, at d_k =
+  // 64, d_v = 128 64.4 against 61.8 and 308 against 287).
+  constexpr bool kDefer = DW == 0 && !(SPLIT && DK == 128);
   static_assert(TILES == 2 || !SPLIT, "fp32 inputs: two tiles per workgroup");
   static_assert(TWO || DW == 0, "a DMA wave fills the other buffer");
   const int tid = threadIdx.x;

@@ -354,12 +354,14 @@ def test_fp32_tail_in_a_workspace_for_one_chain():
     assert torch.equal(mid, chain) and torch.equal(fin, fin2) and torch.equal(o, o2)
 
 
-def test_fp32_forward_beyond_the_chip_bitwise():
+@pytest.mark.parametrize("dk", [64, 128])
+def test_fp32_forward_beyond_the_chip_bitwise(dk):
     # fp32 inputs with outputs: 72 varlen sequences x 4 heads need 1152
     # 32-column workgroups, more than the chip holds, and run in that form over
     # several rounds, longest first; single sequences fit and run the same
-    # body.  States and outputs agree bit for bit.
-    shape = synth.Shape(hk=2, hv=4, dk=128, dv=128, dtype="f32")
+    # body.  States and outputs agree bit for bit.  (At d_k = 64 a chunk's
+    # outputs are stored in the next one, at d_k = 128 at once.)
+    shape = synth.Shape(hk=2, hv=4, dk=dk, dv=128, dtype="f32")
     lens = [1 + (37 * i) % 200 for i in range(72)]
     seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
     p = synth.pack(seqs)
