@@ -245,14 +245,17 @@ def _workspace(nbytes: int, device: torch.device, stream) -> torch.Tensor:
     return ws
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _shape_of(num_seqs, hk, hv, dk, dv, dtype_code, scale):
     return GDNShape(num_seqs, hk, hv, dk, dv, dtype_code, scale)
 
 
 def _shape(num_seqs, hk, hv, dk, dv, dtype_code, scale):
     """The call's gdn_shape, which the library only reads; calls repeat few."""
-    return _shape_of(num_seqs, hk, hv, dk, dv, dtype_code, float(scale))
+    scale = float(scale)
+    if scale == 0.0:      # 0.0 and -0.0 are one key
+        return GDNShape(num_seqs, hk, hv, dk, dv, dtype_code, scale)
+    return _shape_of(num_seqs, hk, hv, dk, dv, dtype_code, scale)
 
 
 def workspace_size(num_seqs: int, num_k_heads: int, num_v_heads: int, d_k: int, d_v: int,

@@ -275,6 +275,19 @@ def test_binding_raises_gdn_error():
         binding._check(2)
 
 
+def test_a_shape_is_taken_by_type_and_sign():
+    # a call's gdn_shape is kept by its values: 1.0 and True are not 1, and a
+    # scale of -0.0 is not 0.0
+    assert gdn.workspace_size(1, 16, 32, 128, 128, [0, 819]) == gdn.workspace_size(1, 16, 32, 128, 128, [0, 819])
+    for bad in ((1.0, 16, 32, 128, 128), (1, 16.0, 32, 128, 128), (1, 16, 32, 128, 128.0)):
+        with pytest.raises(TypeError):
+            gdn.workspace_size(*bad, [0, 819])
+    import math
+    for scale in (0.0, -0.0, 0.0, 1.0):
+        got = binding._shape(1, 16, 32, 128, 128, binding.GDN_BF16, scale).scale
+        assert got == scale and math.copysign(1, got) == math.copysign(1, scale)
+
+
 def test_replay_forward_workspace_is_both_plans():
     # the fused call holds the tail plan (256-byte aligned) then the suffix plan
     lib = gdn.load_library()
