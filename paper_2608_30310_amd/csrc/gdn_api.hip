@@ -122,9 +122,9 @@ gdn_status launch_intra(const gdn_shape& s, const Plan& p, const int32_t* cu, co
 // CU; it is used when its grid fits on the chip at once.  Tail replay
 // whose split grid (the two halves of the chain side by side and the
 // second half's transition) also fits runs split, which halves the chain.
-// When the 32-wide grid does not fit, tail replay of bf16 inputs takes the
-// wide column scan (two tiles per wave, two workgroups per CU: throughput) and
-// everything else the 64-column scan with output waves or the whole-head scan.
+// When the 32-wide grid does not fit, tail replay takes one of the forms of
+// TailScan; with outputs, fp32 inputs stay in it over several rounds and bf16
+// inputs take the 64-column scan with output waves or the whole-head scan.
 gdn_status cols_fit(const gdn_shape& s, bool* fits, uint32_t* col_groups, int* cus_out = nullptr) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||

@@ -155,8 +155,6 @@ __device__ __forceinline__ f32x4 mma_b(const Frag& a, const Frag& b, f32x4 c) {
 // + m of four quarters q at once) spread over twice as many bank groups as
 // without the rotation.
 __device__ __forceinline__ int kslot(int l) { return (l & 48) | ((l + 4 * (l >> 4)) & 15); }
-// The lane whose 16 bytes sit at position p (the inverse of kslot).
-__device__ __forceinline__ int kslot_inv(int p) { return (p & 48) | ((p + 16 - 4 * (p >> 4)) & 15); }
 
 // ---------------------------------------------------------------- key rows in LDS
 // bf16 key (and query) rows lie in LDS as they lie in memory, RB = 2 d_k bytes

@@ -132,7 +132,7 @@ gdn_status check_shape(const gdn_shape* shape, std::string* err) {
   if (!std::isfinite(shape->scale)) { *err = "scale must be finite"; return GDN_ERR_BAD_SHAPE; }
   if (hv > 65535) { *err = "num_v_heads must be <= 65535"; return GDN_ERR_UNSUPPORTED; }
   // A grid dimension counts at most 2^32 - 1 work items; every kernel uses at
-  // most 256 threads per workgroup and at most 4 workgroups per (sequence, head).
+  // most 1024 of them per (sequence, head).
   if (static_cast<int64_t>(N) * hv * 4 > kMaxGroups) {
     *err = "num_seqs * num_v_heads too large";
     return GDN_ERR_UNSUPPORTED;

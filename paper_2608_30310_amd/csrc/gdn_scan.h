@@ -161,18 +161,16 @@ struct ChunkSrc {
 // DMA job j of a chunk of fp32 inputs (0 <= j < L::kJobs) into LDS buffer `base`.
 template <typename L, typename TIn>
 __device__ __forceinline__ void dma_job(const ChunkSrc& c, int64_t vrow, lds_byte* base, int j, int lane) {
+  static_assert(L::kPJobs == 0, "fp32 inputs: the output waves read P from memory");
   if (j < L::kKJobs) {
     dma16_at(c.krec + 1024 * j, 16u * lane, base + L::kOffK + 1024 * j);
   } else if (j < L::kKJobs + L::kTJobs) {
     const int t = j - L::kKJobs;
     dma16_at(c.trec + 1024 * t, 16u * lane, base + L::kOffT + 1024 * t);
-  } else if (j < L::kKJobs + L::kTJobs + L::kPJobs) {
-    const int t = j - L::kKJobs - L::kTJobs;
-    dma16_at(c.prec + 1024 * t, 16u * lane, base + L::kOffP + 1024 * t);
-  } else if (j < L::kKJobs + L::kTJobs + L::kPJobs + L::kVJobs) {
+  } else if (j < L::kKJobs + L::kTJobs + L::kVJobs) {
     // V rows; pad rows repeat the last row (their beta is 0, so they add nothing)
     dma_rows<L::kVRowBytes>(static_cast<const TIn*>(c.v0), vrow, c.clen, base + L::kOffV,
-                            j - L::kKJobs - L::kTJobs - L::kPJobs, lane);
+                            j - L::kKJobs - L::kTJobs, lane);
   } else if (j == L::kJobs - 2) {
     dma16_at(c.srow, 16u * lane, base + L::kOffS);                 // scalars, bytes 0..1023
   } else if (lane < 16) {
@@ -226,8 +224,8 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, i
                                            unsigned char* xm = nullptr) {
   static_assert(!(FWD && EXPORT), "a wave that exports Delta leaves the outputs to another");
   constexpr bool SPLIT = L::kSplit;
+  static_assert(!(FWD && SPLIT), "fp32 inputs leave the outputs to output waves");
   constexpr int NT = DK / 16, NK = DK / 32;
-  constexpr int NKA = ka_frags(DK);
   constexpr int NKF = L::kKFrags;
   constexpr int VRB = L::kVRowBytes;
   const int lg = lane / 16, lr = lane % 16;
@@ -235,13 +233,13 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, i
   const u32x4* tf = reinterpret_cast<const u32x4*>(base + L::kOffT);
   const float* sc = reinterpret_cast<const float*>(base + L::kOffS);
   const unsigned char* vtile = base + L::kOffV;
-  // fragment f of the K record (`nf` fragments per bf16 part; the lo part
-  // exists for fp32 inputs only), lanes in kslot order
+  // fp32 inputs: fragments of the K record, lanes in kslot order; bf16 inputs:
+  // the rows themselves, the queries' behind the keys'
   const int klane = kslot(lane);
-  const KeyTile<DK> kt{base + L::kOffK, lane};   // bf16 inputs: the rows themselves
+  const KeyTile<DK> kt{base + L::kOffK, lane};
   auto ldf = [&](Frag& x, int ti, int kk, bool isq) __attribute__((always_inline)) {
     if constexpr (SPLIT) {
-      const int f = (isq ? NKA : 0) + ti * NK + kk;
+      const int f = ti * NK + kk;
       x.hi = __builtin_bit_cast(bf16x8, kf[f * kWave + klane]);
       x.lo = __builtin_bit_cast(bf16x8, kf[(NKF + f) * kWave + klane]);
     } else {
@@ -337,7 +335,7 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, i
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
       km[u] = mma_km(ka0[u][kk], mb[kk], km[u]);
-      if constexpr (FWD) qm[u] = mma_b<SPLIT>(mb[kk], qa0[u][kk], qm[u]);
+      if constexpr (FWD) qm[u] = mma_b<false>(mb[kk], qa0[u][kk], qm[u]);
     }
   }
 #pragma unroll
@@ -360,7 +358,7 @@ __device__ __forceinline__ void chunk_step(const unsigned char* base, int vc0, i
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
       km[2 + u] = mma_km(ka1[u][kk], mb[kk], km[2 + u]);
-      if constexpr (FWD) qm[2 + u] = mma_b<SPLIT>(mb[kk], qa1[u][kk], qm[2 + u]);
+      if constexpr (FWD) qm[2 + u] = mma_b<false>(mb[kk], qa1[u][kk], qm[2 + u]);
     }
   }
   auto make_r = [&](int ti) __attribute__((always_inline)) {
@@ -844,7 +842,7 @@ struct RecordDma {
   static constexpr int kPerWave = (L::kJobs + NW - 1) / NW;
   ChunkSrc c;
   int w, lane, left;
-  int64_t vrow, k_b, t_b, p_b, s_b;   // elements between value rows; bytes between chunks' records
+  int64_t vrow, k_b, t_b, s_b;   // elements between value rows; bytes between chunks' records
   __device__ __forceinline__ void start(const ScanUnit& u, int ci, int wave, int lane_, int hk, int hv, int dv,
                                         int col0, const TIn* vin, const TIn* kin, const TIn* qin, const u32x4* Kw,
                                         const u32x4* Tw, const float* Sw, const u32x4* Pw) {
@@ -855,11 +853,10 @@ struct RecordDma {
     vrow = static_cast<int64_t>(hv) * dv;
     k_b = static_cast<int64_t>(hk) * L::kKBytes;
     t_b = static_cast<int64_t>(hv) * L::kTBytes;
-    p_b = static_cast<int64_t>(hv) * static_cast<int64_t>(kPRecordBytes);
     s_b = static_cast<int64_t>(hv) * L::kSBytes;
   }
   __device__ __forceinline__ void jobs(lds_byte* base, int j0, int j1, bool values = true) const {
-    constexpr int kV0 = L::kKJobs + L::kTJobs + L::kPJobs;   // first value row job
+    constexpr int kV0 = L::kKJobs + L::kTJobs;   // first value row job
 #pragma unroll
     for (int jj = j0; jj < j1; ++jj) {
       const int j = w + NW * jj;
@@ -870,7 +867,6 @@ struct RecordDma {
   __device__ __forceinline__ void next() {
     c.krec += k_b;
     c.trec += t_b;
-    c.prec += p_b;
     c.srow += s_b;
     c.v0 = static_cast<const TIn*>(c.v0) + vrow * kChunk;
     left -= kChunk;
@@ -934,7 +930,7 @@ constexpr int kColsPerGroup = 32;
 // With outputs: roles of the workgroup's waves (waves go to the four SIMDs in
 // turn).
 constexpr int kOutTiles = 4, kOutCols = 16 * kOutTiles;   // of a throughput workgroup with outputs
-enum ColsRole { kRoleChain, kRoleOut, kRoleDma, kRoleIdle };
+enum ColsRole { kRoleChain, kRoleOut, kRoleDma };
 constexpr int cols_dma_waves(bool split, int tiles) { return split || tiles == kOutTiles ? 0 : 1; }
 constexpr int cols_threads(bool fwd, bool split, int tiles = 2) {
   return (fwd ? 2 * tiles + cols_dma_waves(split, tiles) : 3) * kWave;
@@ -953,7 +949,7 @@ template <typename TIn, int DK, int COLS = kColsPerGroup>
 using ColsLds = ScanLds<TIn, DK, COLS, false, false>;
 
 // Tail replay of bf16 inputs whose grid does not fit on the chip at once (a
-// throughput batch) runs the wide column scan: COLS = 128 columns (a whole
+// throughput batch) may run the wide column scan (see TailScan): COLS = 128 columns (a whole
 // head; 64 for d_v = 64) per workgroup, two 16-column tiles per compute wave
 // (chunk_step_tiles: the K, T and K^T operands are read from LDS once for both
 // tiles), no DMA wave (each compute wave issues a share of the next chunk's
@@ -1066,17 +1062,10 @@ __device__ __forceinline__ void scan_cols_body(lds_byte* lds_l, int block, int n
     }
     __syncthreads();
     for (int j = 0; j < nch; ++j) {
-      const int b = L::kBuffers == 2 ? (j & 1) : 0;
-      if (dma_wave && L::kBuffers == 2 && j + 1 < nch) {
+      const int b = j & 1;
+      if (dma_wave && j + 1 < nch) {
         dma.chunk(lds_l + (b ^ 1) * L::kBytes, !ident);   // lands while the compute waves work on buffer b
         wait_dma();
-      }
-      if (L::kBuffers == 1) {
-        __syncthreads();   // the compute waves are done with the only buffer
-        if (dma_wave && j + 1 < nch) {
-          dma.chunk(lds_l, !ident);
-          wait_dma();
-        }
       }
       __syncthreads();     // next chunk's operands are in LDS; this buffer is free
     }
@@ -1358,11 +1347,11 @@ void k_scan_cols(const int32_t* __restrict__ cu, int32_t hk, int32_t hv, int32_t
   }
 }
 
-// The 32-column scan with output waves over the P sequences `order` names
-// (all of them, in index order, when its n is 0; grid P x Hv x d_v / 32, any
-// number of rounds): the forward of the sequences peeled off a whole-head
-// grid's partly empty last round, and of fp32 batches that do not fit on the
-// chip (see launch_scan).
+// The scan with output waves, 16 TILES columns per workgroup, over the P
+// sequences `order` names (all of them, in index order, when its n is 0; grid
+// P x Hv x d_v / (16 TILES), any number of rounds): TILES = 2 for fp32 batches
+// that do not fit on the chip, TILES = 4 for bf16 batches and for the sequences
+// peeled off a whole-head grid's partly empty last round (see launch_scan).
 template <typename TIn, int DK, int TILES>
 __global__ __launch_bounds__(cols_threads(true, sizeof(TIn) == 4, TILES))
 __attribute__((amdgpu_waves_per_eu(TILES == kOutTiles ? 2 : 1, TILES == kOutTiles ? 2 : 1)))
@@ -1389,12 +1378,12 @@ void k_scan_cols_wide(const int32_t* __restrict__ cu, const SeqOrder order, int3
                                                            kin, Kw, Tw, Sw, state_out, SplitOut{}, &order);
 }
 
-// Tail replay of bf16 inputs, 64 columns per workgroup: one 16-column tile per
-// compute wave beside a DMA wave (the chains of the split scan's second half,
-// which finish a chunk sooner than the wide scan's two-tile waves), grid
-// P x Hv x d_v / 64 over the P sequences `order` names (all of them when its
-// n is 0).  Used for batches whose grid takes at most three rounds of the
-// chip, and for the sequences of a wide grid's partly empty last round.
+// Tail replay, 64 columns per workgroup: one 16-column tile per compute wave
+// beside a DMA wave (the chains of the split scan's second half, which finish a
+// chunk sooner than the wide scan's two-tile waves), grid P x Hv x d_v / 64 over
+// the P sequences `order` names (all of them when its n is 0).  Used for batches
+// whose grid fits on the chip, for those that run in rounds of it (see
+// TailScan), and for the sequences of a wide grid's partly empty last round.
 template <typename TIn, int DK>
 __global__ __launch_bounds__((kSplitCols2 / 16 + 1) * kWave)
 void k_scan_cols_64(const int32_t* __restrict__ cu, const SeqOrder order, int32_t hk, int32_t hv, int32_t dv,
