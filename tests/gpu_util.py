@@ -1,10 +1,13 @@
 """Helpers shared by the GPU tests: host arrays -> device tensors, error metrics."""
 from __future__ import annotations
 
+import dataclasses
+
 import numpy as np
 import torch
 
 import oracle
+import synth
 
 STATE_TOL = 2e-3     # max relative Frobenius error per (sequence, head) state
 OUTPUT_TOL = 5e-3    # max relative Frobenius error per (sequence, head) output block
@@ -60,3 +63,21 @@ def output_err(got, want, cu):
             num = np.linalg.norm(got[a:b, h] - want[a:b, h])
             worst = max(worst, num / den if den > 0 else num)
     return worst
+
+
+def slow_decay(t):
+    """The tokens with beta x 0.1; with a gate scale of 0.002 or less the state
+    forgets slowly, so that what a first half of a long sequence leaves in it
+    weighs (with the usual gates it is ~1e-7 of the state and less)."""
+    return dataclasses.replace(t, beta=(t.beta * 0.1).astype(np.float32))
+
+
+def first_half_share(t):
+    """The first half's share of a sequence's final state by the oracle: the
+    chunks that the kernels' two halves split it into."""
+    nch = (t.q.shape[0] + 63) // 64
+    c1 = 64 * ((27 * nch + 25) // 50)
+    second = dataclasses.replace(t, q=t.q[c1:], k=t.k[c1:], v=t.v[c1:], g=t.g[c1:], beta=t.beta[c1:])
+    _, w = oracle_run(synth.pack([t]))
+    _, w2 = oracle_run(synth.pack([second]))
+    return np.linalg.norm(w - w2) / np.linalg.norm(w)

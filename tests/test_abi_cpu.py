@@ -124,12 +124,17 @@ def test_workspace_size_values():
     st, nl64 = _ws_size(_shape(d_k=64), _cu([0, 1300]))
     assert st == 0 and nl64 == (21 * 32 * (t_rec + s_rec) + 21 * 16 * krec(dk=64)
                                 + 32 * 64 * 128 * 4 + 32 * 64 * 64 * 4)
-    # with outputs, fp32 inputs, or two sequences at 32 heads (512 split
-    # workgroups, more than the chip): no split regions
+    # with outputs, two sequences at 32 heads (512 split workgroups, more than
+    # the chip), or fp32 inputs of fewer than 24 chunks: no split regions
     st, nlf = _ws_size(_shape(), _cu([0, 1300]), 1)
     assert st == 0 and nlf == 21 * 32 * (t_rec + p_rec + s_rec) + 21 * 16 * krec(outputs=True)
     st, nl32 = _ws_size(_shape(qkv_dtype=binding.GDN_F32), _cu([0, 1300]))
     assert st == 0 and nl32 == 21 * 32 * (2 * t_rec + s_rec) + 21 * 16 * krec(split=True)
+    f32 = lambda slots: slots * 32 * (2 * t_rec + s_rec) + slots * 16 * krec(split=True)
+    st, n23 = _ws_size(_shape(qkv_dtype=binding.GDN_F32), _cu([0, 64 * 23]))
+    assert st == 0 and n23 == f32(23)
+    st, n24 = _ws_size(_shape(qkv_dtype=binding.GDN_F32), _cu([0, 64 * 23 + 1]))
+    assert st == 0 and n24 == f32(24) + 32 * 128 * 128 * 4 * 2
     # slots 0..20, then 1300/64 + 1 = 21 .. 41
     st, n2l = _ws_size(_shape(num_seqs=2), _cu([0, 1300, 2600]))
     assert st == 0 and n2l == 42 * 32 * (t_rec + s_rec) + 42 * 16 * krec()

@@ -13,7 +13,8 @@ import torch
 
 import paper_2608_30310_amd as gdn
 import synth
-from tests.gpu_util import STATE_TOL, OUTPUT_TOL, device_inputs, oracle_run, state_err, to_f64
+from tests.gpu_util import (STATE_TOL, OUTPUT_TOL, device_inputs, first_half_share, oracle_run, slow_decay, state_err,
+                            to_f64)
 
 pytestmark = pytest.mark.gpu
 
@@ -169,13 +170,13 @@ def test_adversarial_repeated_keys():
 
 
 def test_whole_head_and_column_kernels_agree():
-    # 72 sequences x 4 heads exceed the chip with the column-split scan (one
-    # workgroup per 32 columns), so the batch's tail replay runs on the wide
-    # column scan (two tiles per wave) and its forward on the whole-head
-    # kernel; single sequences run on the 32-wide column scan (one tile per
-    # wave).  Same products in the same order: the replayed states agree bit
-    # for bit.
-    lens = [1 + (37 * i) % 200 for i in range(72)]
+    # 72 sequences of three chunks x 4 heads exceed the chip with the
+    # column-split scan (one workgroup per 32 columns), so the batch's tail
+    # replay runs on the wide column scan (two tiles per wave) and its forward
+    # on the whole-head kernel; single sequences run on the 32-wide column scan
+    # (one tile per wave).  Same products in the same order: the replayed states
+    # agree bit for bit.
+    lens = [129 + (37 * i) % 64 for i in range(72)]
     seqs = [_seq(i, n) for i, n in enumerate(lens)]
     x = device_inputs(synth.pack(seqs))
     st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
@@ -195,12 +196,12 @@ def test_whole_head_and_column_kernels_agree():
 
 @pytest.mark.parametrize("nseq", [3, 12, 36])
 def test_one_tile_and_wide_batches_bitwise(nseq):
-    # 3 and 12 sequences at 32 value heads run in the 64-column one-tile scan
-    # (at most three rounds of MI355X's 256 CUs); 36 run wide (1152
-    # workgroups, two per CU), whose last round would be a quarter full, so
-    # the four shortest run in the one-tile scan after it.  Every sequence's
-    # state must be bitwise that of its own call (the one-tile, two-tile and
-    # 32-column chains run the same products).
+    # 3 sequences at 32 value heads run in the 64-column one-tile scan, which
+    # fits on MI355X's 256 CUs; 12 and 36 run wide (384 and 1152 workgroups, two
+    # per CU); the last round of 36 would be a quarter full, so the four
+    # shortest run in the one-tile scan after it.  Every sequence's state must
+    # be bitwise that of its own call (the one-tile, two-tile and 32-column
+    # chains run the same products).
     shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="bf16")
     lens = [64 + (37 * i) % 200 for i in range(nseq)]
     seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
@@ -213,13 +214,14 @@ def test_one_tile_and_wide_batches_bitwise(nseq):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("lens", [[200] * 9, [1200, 1] + [70, 0, 64, 65, 10, 3, 1], [700, 650] + [300] * 15 + [0]],
-                         ids=["even", "one_long", "two_per_cu"])
+@pytest.mark.parametrize("lens", [[200] * 9, [1200, 1] + [70, 0, 64, 65, 10, 3, 1], [700, 650] + [300] * 15 + [0],
+                                  [300] * 36 + [1, 0, 64, 65]], ids=["even", "one_long", "two_per_cu", "many"])
 def test_tail_batches_in_rounds_and_all_resident_bitwise(lens, d):
     # 32 value heads beyond the chip: even batches run two tiles per wave with
-    # every workgroup resident from the start, batches with one long chain in
-    # rounds of 64-column workgroups.  States agree bit for bit with each
-    # sequence's own call (below 20 chunks: one chain) either way.
+    # every workgroup resident from the start (at d = 64 only the last one, five
+    # rounds of 64 columns), batches with one long chain in rounds of 64-column
+    # workgroups.  States agree bit for bit with each sequence's own call (below
+    # 20 chunks: one chain) either way.
     shape = synth.Shape(hk=16, hv=32, dk=d, dv=d, dtype="bf16")
     seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
     x = device_inputs(synth.pack(seqs))
@@ -232,14 +234,14 @@ def test_tail_batches_in_rounds_and_all_resident_bitwise(lens, d):
 
 @pytest.mark.parametrize("nseq,d", [(12, 128), (36, 128), (12, 64)])
 def test_forward_batches_with_a_peeled_last_round(nseq, d):
-    # 12 and 36 sequences at 32 value heads run the forward on the whole-head
-    # kernel (384 and 1152 workgroups, one per CU); the last round would hold
-    # 128 of 256, so the four shortest sequences run in the 32-column scan
-    # with output waves after it.  States agree bit for bit with each
+    # 12 and 36 sequences at 32 value heads of d_v = 128 run the forward on the
+    # whole-head kernel (384 and 1152 workgroups, one per CU); the last round
+    # would hold 128 of 256, so the four shortest sequences run in the 64-column
+    # scan with output waves after it.  States agree bit for bit with each
     # sequence's own call (same products, same order); outputs to within one
     # bf16 rounding (the whole-head kernel sums the output's two terms in
-    # another order).  At d = 64 the same holds with two 32-column groups per
-    # head.
+    # another order).  At d = 64 a head is one 64-column workgroup and all run
+    # so, in two rounds.
     shape = synth.Shape(hk=16, hv=32, dk=d, dv=d, dtype="bf16")
     lens = [64 + (37 * i) % 200 for i in range(nseq)]
     seqs = [_seq(i, n, shape=shape) for i, n in enumerate(lens)]
@@ -285,11 +287,15 @@ def test_fp32_tail_in_two_halves_and_in_64_columns(dk, dv):
     # fp32 tails of 24 chunks and more on a grid that fits run as two
     # half-length chains and a combine: against the oracle within four times the
     # split operands' error (5e-6 measured over the declared sizes), and the
-    # fused call bit for bit.  A batch beyond the chip runs one chain per 64
-    # columns: bit for bit each sequence's own call where that is one chain too.
+    # fused call bit for bit.  The gates decay slowly, so the first half is a
+    # fifth of the state and more: a wrong transition or combine shows.  A batch
+    # beyond the chip runs one chain a head (d_v = 128) or per 64 columns: bit
+    # for bit each sequence's own call where that is one chain too.
     shape = synth.Shape(hk=2, hv=4, dk=dk, dv=dv, dtype="f32")
     lens = [64 * 20 + 5, 63, 0, 64 * 23 + 1, 64 * 25]
-    p = synth.pack([_seq(i, n, shape=shape) for i, n in enumerate(lens)])
+    seqs = [slow_decay(_seq(i, n, shape=shape, gate_scale=0.002)) for i, n in enumerate(lens)]
+    assert min(first_half_share(t) for t, n in zip(seqs, lens) if n > 64) > 0.15
+    p = synth.pack(seqs)
     x = device_inputs(p)
     st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
     _, want = oracle_run(p)
@@ -331,10 +337,8 @@ def test_fp32_tail_in_a_workspace_for_one_chain():
     # batch whose split grid does not fit on the chip, in tail_replay, in the
     # fused call and (there against the two halves, within the split operands'
     # error) in the state-only layer.
-    import dataclasses
     shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="f32")
-    t = synth.tokens(211, 0, 0, 0, 1536, shape, gate_scale=0.002)
-    t = dataclasses.replace(t, beta=(t.beta * 0.1).astype(np.float32))
+    t = slow_decay(synth.tokens(211, 0, 0, 0, 1536, shape, gate_scale=0.002))
     x, x2 = device_inputs(synth.pack([t])), device_inputs(synth.pack([t, t]))
     halves = 32 * 128 * (128 + 128) * 4
     ws = torch.empty(gdn.workspace_size(1, 16, 32, 128, 128, [0, 1536], dtype=torch.float32) - halves,
@@ -352,6 +356,36 @@ def test_fp32_tail_in_a_workspace_for_one_chain():
                                      workspace=ws)
     o2, fin2 = gdn.chunk_forward(y["q"], y["k"], y["v"], y["g"], y["beta"], y["cu"], y["cu_host"], state_in=chain)
     assert torch.equal(mid, chain) and torch.equal(fin, fin2) and torch.equal(o, o2)
+
+
+@pytest.mark.parametrize("chunks", [31, 32, 33])
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 64), (128, 64), (64, 128)])
+def test_forward_dma_two_chunks_ahead_bitwise(dk, dv, chunks):
+    # From 32 chunks on the DMA wave of a forward runs two chunks ahead.  Single
+    # sequences run 16 columns per workgroup, as many as fill the chip 32, both
+    # with three buffers; twice as many run 64 columns, whose output waves fetch
+    # one chunk ahead at any length.  Same products, same order: bit for bit.
+    hk, hv = 16, 32
+    fill = 256 * 32 // (hv * dv)
+    lens = [64 * chunks - 5, 64 * (chunks - 1) + 1] * fill
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    T = sum(lens)
+    rn = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    unit = lambda t: (t / t.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    q, k, v = unit(rn(T, hk, dk)), unit(rn(T, hk, dk)), rn(T, hv, dv).to(torch.bfloat16)
+    g, beta = -torch.nn.functional.softplus(rn(T, hv)) * 0.02, torch.sigmoid(rn(T, hv))
+    s0 = rn(len(lens), hv, dk, dv) * 0.2
+    at = [0] + torch.tensor(lens).cumsum(0).tolist()
+
+    def call(a, b):
+        cu = torch.tensor(at[a:b + 1], dtype=torch.int32) - at[a]
+        t = slice(at[a], at[b])
+        return gdn.chunk_forward(q[t], k[t], v[t], g[t], beta[t], cu.cuda(), cu, state_in=s0[a:b].contiguous())
+
+    o, st = call(0, len(lens))
+    for a, b in ((0, fill), (0, 1), (1, 2)):
+        oi, si = call(a, b)
+        assert torch.equal(st[a:b], si) and torch.equal(o[at[a]:at[b]], oi), f"sequences {a} to {b}"
 
 
 @pytest.mark.parametrize("dk", [64, 128])
@@ -401,7 +435,8 @@ def test_replay_forward_equals_the_two_calls_bitwise(case):
     # the fused call runs the same kernels (the suffix's chunk preparation
     # beside the tail scan), so it must reproduce tail_replay + chunk_forward
     # "ragged*" covers an empty tail and an empty suffix at every (d_k, d_v)
-    # the kernels are built for; "wide" runs the whole-head scan kernel;
+    # the kernels are built for; "wide" runs the wide tail scan and the
+    # whole-head scan kernel;
     # "split*": a 21-chunk tail at 32 heads, which both run in two halves (the
     # fused call with the suffix's preparation beside the split scan, or with
     # no suffix at all)
@@ -418,8 +453,8 @@ def test_replay_forward_equals_the_two_calls_bitwise(case):
         rs, ss = [1300], [0]
     elif case.startswith("ragged"):
         rs, ss = [0, 1, 64, 130, 257], [65, 0, 1, 200, 64]
-    else:   # enough heads that the whole-head scan kernel runs
-        rs = [1 + (37 * i) % 150 for i in range(72)]
+    else:   # enough heads and even enough chains
+        rs = [129 + (37 * i) % 64 for i in range(72)]
         ss = [1 + (53 * i) % 120 for i in range(72)]
     tails = synth.pack([_seq(i, r, start=0, shape=shape) for i, r in enumerate(rs)])
     sufs = synth.pack([_seq(i, s, start=r, shape=shape) for i, (r, s) in enumerate(zip(rs, ss))])
@@ -474,8 +509,10 @@ def test_varlen_graph_with_longest_first_order():
     in the kernels' arguments.  Tail replay and forward captured in one HIP
     graph replay bitwise like the eager calls, three times, with other eager
     work between the replays."""
-    shape = synth.Shape(hk=8, hv=16, dk=128, dv=128, dtype="bf16")
-    lens = [70, 700, 3, 300, 1000, 64]          # 6 x 16 x 4 = 384 column groups > 256 CUs
+    shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="bf16")
+    # 320 heads, more than the 256 CUs hold one of; the two shortest of the
+    # forward's run in 64 columns after the rest
+    lens = [700, 600, 70, 650, 640, 700, 300, 710, 64, 690]
     p = synth.pack([_seq(i, n, shape=shape) for i, n in enumerate(lens)])
     x = device_inputs(p)
     n = len(lens)

@@ -14,7 +14,7 @@ import oracle
 import paper_2608_30310_amd as gdn
 import synth
 from synth import workloads
-from tests.gpu_util import (OUTPUT_TOL, STATE_TOL, device_inputs, oracle_run, output_err,
+from tests.gpu_util import (OUTPUT_TOL, STATE_TOL, device_inputs, first_half_share, oracle_run, output_err, slow_decay,
                             state_err, to_f64)
 
 pytestmark = pytest.mark.gpu
@@ -59,35 +59,39 @@ def test_ragged_varlen(dtype, dk, dv, grp):
     assert torch.equal(st2[0], torch.from_numpy(s0[0]).cuda())
 
 
-# 72 short sequences: with 4 value heads the column-split grid is 72 x 4 x d_v/32
-# >= 576 workgroups, more than the 256 CUs, so the forward runs on the
-# whole-head scan kernel, and so does the fp32 tail replay; the bf16 tail
-# replay runs on the wide column scan (two 16-column tiles per wave)
+# Batches of 4 value heads beyond the chip.  72 short sequences: tails run in
+# rounds of 64 columns, fp32 ones of d_v = 128 a head per workgroup; forwards a
+# head per workgroup with a peeled last round (bf16, d_v = 128), in 64 columns
+# (bf16, d_v = 64) or in 32 (fp32).  220 sequences of three chunks: bf16 tails
+# run the wide scan (two 16-column tiles per wave) at every (d_k, d_v), with a
+# peeled last round.
 WIDE_LENS = [1 + (37 * i) % 200 for i in range(72)]
+EVEN_LENS = [129 + (37 * i) % 64 for i in range(220)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (64, 128), (128, 64)])
-def test_wide_batch_whole_head_kernel(dtype, dk, dv):
+@pytest.mark.parametrize("lens", [WIDE_LENS, EVEN_LENS], ids=["ragged", "even"])
+def test_batches_beyond_the_chip(dtype, dk, dv, lens):
     shape = synth.Shape(hk=2, hv=4, dk=dk, dv=dv, dtype=dtype)
-    seqs = [synth.tokens(101, 0, i, 0, n, shape) for i, n in enumerate(WIDE_LENS)]
+    seqs = [synth.tokens(101, 0, i, 0, n, shape) for i, n in enumerate(lens)]
     p = synth.pack(seqs)
     x = device_inputs(p)
     st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
     _, want = oracle_run(p)
     e_tail = state_err(to_f64(st), want)
     rng = np.random.default_rng(8)
-    s0 = (rng.standard_normal((len(WIDE_LENS), shape.hv, dk, dv)) * 0.3).astype(np.float32)
+    s0 = (rng.standard_normal((len(lens), shape.hv, dk, dv)) * 0.3).astype(np.float32)
     o, st2 = gdn.chunk_forward(x["q"], x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"],
                                state_in=torch.from_numpy(s0).cuda(), scale=0.5)
     wo, ws = oracle_run(p, state_in=s0.astype(np.float64), outputs=True, scale=0.5)
     e_st = state_err(to_f64(st2), ws)
     e_o = output_err(to_f64(o), wo, p.cu_seqlens)
-    _report(f"wide {dtype} dk={dk} dv={dv}", tail=e_tail, fwd_state=e_st, out=e_o)
+    _report(f"{len(lens)} sequences {dtype} dk={dk} dv={dv}", tail=e_tail, fwd_state=e_st, out=e_o)
     assert e_tail <= STATE_TOL and e_st <= STATE_TOL and e_o <= OUTPUT_TOL
 
 
-# Tail replay in two halves: bf16, at least 20 chunks in the longest sequence
+# Tail replay in two halves: bf16 inputs with at least 20 chunks in the longest sequence
 # and N x Hv x 8 <= 256 workgroups (d = 128).  Lengths cover an empty
 # sequence, one token, two chunks (the second half one chunk), 7 chunks and 21
 # with a ragged end, so every part meets a short or empty range somewhere.
@@ -98,28 +102,16 @@ def test_wide_batch_whole_head_kernel(dtype, dk, dv):
 SPLIT_LENS = [0, 1, 70, 400, 1300]
 
 
-def _slow_decay(t):
-    import dataclasses
-    return dataclasses.replace(t, beta=(t.beta * 0.1).astype(np.float32))
-
-
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (64, 128), (128, 64)])
 def test_split_tail_replay_ragged(dk, dv):
     shape = synth.Shape(hk=2, hv=4, dk=dk, dv=dv, dtype="bf16")
-    seqs = [_slow_decay(synth.tokens(102, 0, i, 0, n, shape, gate_scale=0.002))
+    seqs = [slow_decay(synth.tokens(102, 0, i, 0, n, shape, gate_scale=0.002))
             for i, n in enumerate(SPLIT_LENS)]
     p = synth.pack(seqs)
     x = device_inputs(p)
     st = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
     _, want = oracle_run(p)
-    # the longest sequence's second half alone (split point as the kernel takes it)
-    nch = (SPLIT_LENS[-1] + 63) // 64
-    c1 = 64 * ((24 * nch + 21) // 43)
-    t = seqs[-1]
-    import dataclasses
-    second = dataclasses.replace(t, q=t.q[c1:], k=t.k[c1:], v=t.v[c1:], g=t.g[c1:], beta=t.beta[c1:])
-    _, w2 = oracle_run(synth.pack([second]))
-    share = np.linalg.norm(want[-1] - w2[0]) / np.linalg.norm(want[-1])
+    share = first_half_share(seqs[-1])
     e = state_err(to_f64(st), want)
     _report(f"split bf16 dk={dk} dv={dv}", tail=e, first_half_share=share)
     assert share > 0.1

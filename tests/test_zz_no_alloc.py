@@ -2,8 +2,9 @@
 
 The entry point that allocates nothing takes its workspace from the library's
 own device array; its states must equal those of gdn_tail_replay, which uses a
-caller-owned workspace and the same kernels, bit for bit.  Two calls in a
-row, the second with a smaller input (the array keeps the first call's
+caller-owned workspace and the same kernels, bit for bit (fp32 tails whose two
+halves' states the array has no room for run as one chain and differ from a call
+with a full workspace by rounding order).  Two calls in a row, the second with a smaller input (the array keeps the first call's
 records, which the second must not read), the first long enough to run the
 split tail replay; both also checked against the fp64 oracle.
 """
@@ -13,7 +14,7 @@ import torch
 
 import paper_2608_30310_amd as gdn
 import synth
-from tests.gpu_util import STATE_TOL, device_inputs, oracle_run, state_err, to_f64
+from tests.gpu_util import STATE_TOL, device_inputs, first_half_share, oracle_run, slow_decay, state_err, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -48,18 +49,29 @@ def test_noalloc_matches_tail_replay_twice():
 
 
 def test_noalloc_runs_one_chain_where_the_halves_do_not_fit():
-    # 4480 fp32 tokens: the chunk records take 62.5 of the 64 MiB, the halves'
-    # states 4 more, so the call runs as one chain.  The two forms differ by
-    # rounding order alone (each within 5e-6 of the exact state).
+    # 4480 fp32 tokens: the chunk records take all but 16 KiB of the 64 MiB, the
+    # halves' states 4 MiB more, so the call runs as one chain: bit for bit the
+    # call whose workspace ends with the records.  The gates decay slowly, so that
+    # the first half weighs in the comparison with the two halves, which differ
+    # from one chain by rounding order alone (each within 5e-6 of the exact state).
     shape = synth.Shape(hk=16, hv=32, dk=128, dv=128, dtype="f32")
-    p, x = _case(2, [4480], shape)
+    t = slow_decay(synth.tokens(502, 0, 0, 0, 4480, shape, gate_scale=0.0005))
+    assert first_half_share(t) > 0.15
+    p = synth.pack([t])
+    x = device_inputs(p)
     need = gdn.workspace_size(1, 16, 32, 128, 128, [0, 4480], dtype=torch.float32)
-    assert need > gdn.noalloc_scratch_bytes()
-    want = gdn.tail_replay(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    records = need - 32 * 128 * (128 + 128) * 4
+    assert records == gdn.noalloc_scratch_bytes() - (16 << 10) < need
+    args = (x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"])
+    want = gdn.tail_replay(*args)
+    chain = gdn.tail_replay(*args, workspace=torch.empty(records, dtype=torch.uint8, device="cuda:0"))
     got = torch.full((1, 32, 128, 128), float("nan"), device="cuda:0")
-    gdn.tail_replay_noalloc(x["k"], x["v"], x["g"], x["beta"], x["cu"], x["cu_host"], got)
+    gdn.tail_replay_noalloc(*args, got)
     torch.cuda.synchronize()
+    assert torch.equal(got, chain)
     assert state_err(to_f64(got), to_f64(want)) <= 2e-5
+    _, w = oracle_run(p)
+    assert state_err(to_f64(got), w) <= 2e-5
 
 
 def test_noalloc_rejects_oversized_input():
