@@ -97,7 +97,7 @@ gdn_status gdn_workspace_size(const gdn_shape* shape,
  * linear in the first half's state, so it is formed as the second half's
  * transition applied to the first half's state plus the second half's state
  * from zero.  The result equals the one-chain evaluation up to rounding order
- * (about 1e-6 relative); below those sizes it is the one-chain evaluation.
+ * (5e-6 relative measured); below those sizes it is the one-chain evaluation.
  * For fp32 inputs the last N x Hv x d_k x (d_v + d_k) x 4 bytes, the halves'
  * states, may be missing from the workspace: the call then evaluates one chain.
  * bf16 inputs need all of gdn_workspace_size(..., 0).

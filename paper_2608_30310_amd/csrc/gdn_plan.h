@@ -130,18 +130,18 @@ int32_t wide_peel(const gdn_shape& s, int64_t cus);
 // when every workgroup of the split grid fits on the chip at once (one per CU):
 // N x Hv x (d_v / 32 + (d_v + d_k) / 64) of them, at most kSplitMaxGroups (the
 // MI355X's 256 CUs; fewer on a smaller device are checked at launch), and
-// the longest sequence has at least split_min_chunks chunks.  Measured on
-// MI355X: one chain of n chunks takes ~1.63 n + 2 us, the split ~1.06 n + 9.4
-// (its chunks are slower with every CU busy, and the combine with the kernel
-// boundary before it costs ~7 us), even at n = 13 and ahead beyond.  fp32 inputs
-// (three passes per product): ~1.9 n + 2 us against ~1.15 n + 6 (20 chunks 39.9
-// -> 31.2 us, 52 chunks 98.6 -> 67).
+// the longest sequence has at least split_min_chunks chunks.  Whole calls, one
+// sequence at 16/32 heads of d = 128, one chain against two halves: bf16 10
+// chunks 22.5 and 24.8 us, 13 26.2 and 26.6, 16 29.8 and 29.0, 19 34.2 and 31.1,
+// 26 43.3 and 34.9; fp32 10 29.3 and 30.8, 12 32.8 and 32.7, 16 40.2 and 35.6, 20
+// 48.0 and 41.0, 26 59.0 and 48.8 (the halves' chunks are slower with every CU
+// busy, and the combine with the kernel boundary before it costs ~7 us).
 constexpr int64_t kSplitMaxGroups = 256;
 
+// The halves are ahead from 14 chunks (fp32: 12) on, but the lines lie where the
+// interface has them: shorter tails are the one-chain evaluation, bit for bit
+// the forward's final state, and need the chunk records alone.
 constexpr int32_t kSplitMinChunks = 20;
-// fp32 inputs gain from 20 chunks on as well, but callers have sized their
-// workspaces for one chain there; from 24 chunks on the halves' states add at
-// most a quarter to the chunk records.
 constexpr int32_t kSplitMinChunksF32 = 24;
 constexpr int32_t split_min_chunks(bool f32) { return f32 ? kSplitMinChunksF32 : kSplitMinChunks; }
 // state columns per workgroup of the first and of the second half
